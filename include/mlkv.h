@@ -226,6 +226,14 @@ mlkv_status mlkv_decode_attention(int layer, const void* q, const mlkv_cache* ca
  *             increments them after the step.
  *   out_all: device [l][batch][h][head_dim], fp32 or bf16.
  *   max_len_hint: bound of ctx_lens[b] + 1 (<= 0 means capacity).
+ * Every layer's queries are at hand, so where the map's layers fall into equal
+ * groups of consecutive layers that read the same KV heads and whose first
+ * layer appends them (every uniform map), all layers run in one launch and
+ * each cached row is read once for all layers sharing it.  Other maps, steps
+ * under one of the plan overrides below, and steps of more than about four
+ * million (sequence, KV head) units run layer by layer.  A workspace smaller
+ * than mlkv_workspace_bytes that holds the layer-by-layer step's needs is
+ * accepted; the one-launch step then cuts sequences into fewer runs.
  */
 mlkv_status mlkv_decode_step(const void* q_all, const void* k_new_all, const void* v_new_all,
                              const mlkv_cache* cache, const mlkv_map* map,
@@ -445,7 +453,8 @@ int mlkv_model_fused_path(const mlkv_model* model, int batch);
  * workgroup per pair instead when the pairs number at least 3/8 of the
  * compute units and fewer than the budget.  `max_parts` bounds the
  * workgroups covering one sequence.
- * Environment overrides, read on every call (tests and tuning):
+ * Environment overrides, read on every call (tests and tuning; while one is
+ * set, decode steps run layer by layer, by this plan):
  *   MLKV_WORKGROUPS=n   workgroup budget n instead of the device's;
  *   MLKV_COMBINE=kernel always merge split runs with the separate merge
  *                       kernel (by default the last run of each unit merges
@@ -480,7 +489,8 @@ int mlkv_plan_merge_kernel(const mlkv_map* map, int layer, int batch, int capaci
  * separate merge kernel finishes the split runs of that attention launch, the
  * pair brackets both kernels (start with the attention dispatch, stop when
  * the merge completes), so one timed launch is a layer's whole attention.
- * Separate append kernels are outside the pair.  Up to max_launches launches
+ * Separate append kernels are outside the pair.  A decode step that runs all
+ * layers in one launch is one timed launch.  Up to max_launches launches
  * are recorded; later ones are not timed.  Creates the events (host call, not
  * for capture).  Errors: MLKV_ERR_INVALID_ARG (max_launches <= 0),
  * MLKV_ERR_HIP. */

@@ -134,6 +134,36 @@ struct AttnSideParams : AttnParams {
   SideProduct side;
 };
 
+// The attention of every layer of a decode step in one launch (step.hip), for
+// maps whose layers fall into equal groups of `layers` consecutive layers
+// reading the same kv_per_layer KV heads, appended by the group's first
+// layer.  Unit u is (sequence u / n_kv, KV head u % n_kv); its rows, layer by
+// layer and head by head, number layers * G.
+constexpr int step_max_blocks(int head_dim) { return head_dim == 64 ? 3 : 2; }  // of 16 rows
+struct StepParams {
+  const uint16_t* q;         // [l][B][h][D]
+  const uint16_t* k;         // key plane   [n_kv][B][S][D]
+  const uint16_t* v;         // value plane [n_kv][B][S/32][D][32]
+  const uint16_t* k_new;     // [B][n_kv][D], appended at slot ctx[b]
+  const uint16_t* v_new;
+  const int32_t* ctx;        // [B] tokens cached before the step
+  void* out;                 // [l][B][h][D] fp32 or bf16
+  int* counters;             // [units*chunks] finished runs (zero between calls)
+  float* part_acc;           // [units*chunks][runs][chunk_rows][D]  unnormalised partial outputs
+  float* part_ml;            // [units*chunks][runs][chunk_rows][2]  (max in log2 units, denominator)
+  const double* rope_cs;     // [B][rope_half][2] cos, sin at the token's position, or null
+  int rope_half;
+  int B, h, S, n_kv;
+  int layers, kv_per_layer, G;
+  int chunks, chunk_rows;    // a unit's rows in `chunks` parts of at most chunk_rows
+  int runs, min_tiles;       // most runs of a unit; least tiles of a run when there are several
+  int waves;                 // waves per workgroup: default_waves() or wide_waves()
+  unsigned items;            // units * runs
+  int max_len;               // attended lengths are clamped to this (<= S)
+  int out_bf16;
+  float scale_log2;          // log2(e) / sqrt(D)
+};
+
 // ---- GPT-NeoX layer pieces around attention (model.hip) ----
 struct NormParams {  // h1 = LN1(x), h2 = LN2(x), per row
   const float* x;             // [rows][d]
@@ -227,6 +257,9 @@ hipError_t launch_attention_main(const AttnParams& p, int head_dim, hipStream_t 
 // stop: optional event recorded when the merge kernel completes.
 hipError_t launch_attention_merge(const AttnParams& p, int head_dim, hipStream_t stream,
                                   hipEvent_t stop);
+// Rows of at most 16 * step_max_blocks(head_dim) per chunk; start/stop as above.
+hipError_t launch_step(const StepParams& p, int head_dim, hipStream_t stream, hipEvent_t start,
+                       hipEvent_t stop);
 int max_batch();
 int stage_floats();  // partial-output floats one workgroup can merge in place
 int resident_workgroups(int head_dim); // attention workgroups the device holds at once (0: none)

@@ -25,6 +25,10 @@ struct mlkv_map {
   std::vector<int> kv_begin, kv_count, group;
   // per layer: the KV heads appended form [own_begin, own_begin + own_count)
   std::vector<int> own_begin, own_count;
+  // > 0: the layers fall into groups of this many consecutive layers, each
+  // reading the same number of KV heads, its own, which its first layer
+  // appends (every uniform map): a decode step may take all layers at once.
+  int layers_per_group = 0;
 };
 
 struct mlkv_model {
@@ -111,6 +115,16 @@ std::string analyse(mlkv_map& m) {
       return "the KV heads a layer owns must be contiguous";
     }
   }
+  const int g = m.kv_count[0], groups = n_kv / g;
+  if (n_kv % g == 0 && l % groups == 0) {
+    const int per = l / groups;
+    bool grouped = true;
+    for (int n = 0; n < l; ++n)
+      grouped = grouped && m.kv_count[n] == g && m.kv_begin[n] == n / per * g &&
+                m.own_count[n] == (n % per == 0 ? g : 0) &&
+                (n % per != 0 || m.own_begin[n] == m.kv_begin[n]);
+    if (grouped) m.layers_per_group = per;
+  }
   return "";
 }
 
@@ -136,6 +150,8 @@ mlkv_status check_cache(const mlkv_cache* c, const mlkv_map* map) {
   if (elems > 9.0e18) return fail(MLKV_ERR_CAPACITY, "cache too large");
   return MLKV_OK;
 }
+
+size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int tiles_of(int len) { return (len + kTileTokens - 1) / kTileTokens; }
 
@@ -289,6 +305,77 @@ Plan plan(const mlkv_map* map, int layer, int batch, int max_len, int head_dim) 
   return pl;
 }
 
+// The launch of a whole decode step (step.hip): every (sequence, KV head)
+// unit's query rows, those of all layers reading the head, in `chunks` parts
+// of chunk_rows, and its tiles in up to `runs` runs.  Workspace: the arrival
+// counters, then the runs' partials.
+//
+// chunks: the fewest a wave's registers allow, or, where the units leave
+// compute units idle, chunks of a block less (D = 64: 2 blocks of 16 rows,
+// D = 128: 1) if all of them still fit one per compute unit: each chunk reads
+// the rows again through the caches, but there are fewer runs and rows to
+// merge (MLKV-4, 8 x 8000 tokens 16.0 against 18.0 us, 20 x 2000 tokens 11.4
+// against 13.3 us, one sequence of 32000 tokens 14.1 against 18.7 us; 8 x
+// 32768 tokens 55.2 against 54.2 us).  With more units the extra reads cost
+// more than they save (MLKV-2, 64 sequences of 1000..4000 tokens: 23.8 us in
+// chunks of three blocks, 32 in chunks of two).
+// runs: split only to give every compute unit one workgroup of eight waves
+// (8 x 32768 tokens: 54 us on 256 such workgroups, 64 on 512 of four waves,
+// whose partials are twice as many), in at most kMaxStepRuns runs of a unit
+// (one sequence of 32000 tokens: 16 runs 14.1 us; 32 and 64 runs, merged by
+// one workgroup, were slower).
+// waves: a grid of more than one and at most three workgroups per compute
+// unit is resident at once with four waves and not with eight (128 ragged
+// sequences, 512 units: 42.9 against 45.4 us; 96, 384 units: 34.8 against
+// 35.9); larger grids run in rounds and prefer eight (MHA at 32 sequences,
+// 4608 units: 438 against 444 us; 800 units of 200..4000 tokens 101.5 against
+// 102.8).
+struct StepPlan {
+  int chunks, chunk_rows, runs, waves;
+  long units;
+  size_t ml, need;  // offset of the (max, denominator) pairs, bytes in all; 0 without split runs
+};
+constexpr int kMaxStepRuns = 16;
+constexpr int kMaxStepChunksBySplit = 5;  // chunks a unit may be cut into to fill the device
+
+StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, size_t ws_bytes) {
+  StepPlan pl{};
+  const long cus = compute_units_or_fallback();
+  const int rows = map->layers_per_group * map->group[0];
+  const int blocks = (rows + 15) / 16, most = mlkv::step_max_blocks(head_dim);
+  pl.units = static_cast<long>(batch) * map->n_kv;
+  const int fewest = (blocks + most - 1) / most, finer = (blocks + most - 2) / (most - 1);
+  pl.chunks = finer <= kMaxStepChunksBySplit && pl.units * finer <= cus ? finer : fewest;
+  pl.chunk_rows = (rows + pl.chunks - 1) / pl.chunks;
+  const long groups = pl.units * pl.chunks;  // workgroups without split runs
+  pl.waves = groups > cus && groups <= 3 * cus ? mlkv::default_waves() : mlkv::wide_waves();
+  const long longest = tiles_of(max_len < 1 ? 1 : max_len) / kMinTiles;
+  long runs = cus / groups;
+  runs = runs < longest ? runs : longest;
+  runs = runs < 1 ? 1 : runs > kMaxStepRuns ? kMaxStepRuns : runs;
+  for (;; --runs) {  // as many as the workspace holds
+    pl.runs = static_cast<int>(runs);
+    pl.ml = pl.need = 0;
+    if (runs == 1) return pl;
+    const size_t part_rows = static_cast<size_t>(groups) * runs * pl.chunk_rows;
+    pl.ml = kCounterSlots * sizeof(int32_t) + align_up(part_rows * head_dim * sizeof(float), 256);
+    pl.need = pl.ml + part_rows * 2 * sizeof(float);
+    if (pl.need <= ws_bytes) return pl;
+  }
+}
+
+// Whether a step runs in one launch: the map's layers in equal groups, no
+// override of the per-layer plan, and a grid the device takes (2^32 threads;
+// such a step, of more than 4 million units, runs layer by layer).
+bool step_in_one_launch(const mlkv_map* map, int batch, int head_dim) {
+  if (map->layers_per_group <= 0) return false;
+  for (const char* name : {"MLKV_WORKGROUPS", "MLKV_COMBINE", "MLKV_WIDE"})
+    if (std::getenv(name)) return false;
+  const long rows = static_cast<long>(map->layers_per_group) * map->group[0];
+  const long chunk = 16L * mlkv::step_max_blocks(head_dim);
+  return static_cast<double>(batch) * map->n_kv * ((rows + chunk - 1) / chunk) < (1L << 22);
+}
+
 // Whether launches of this plan record (or follow) a step's run items: split
 // runs scheduled on the device; not a workgroup per unit or one workgroup.
 bool plan_records(const Plan& pl) { return !pl.direct && pl.n_blocks > 1; }
@@ -311,8 +398,6 @@ PlanKey plan_key(const Plan& pl, int kv_count) {
 int max_len_of(const mlkv_cache* cache, int max_len_hint) {
   return max_len_hint <= 0 ? cache->capacity : max_len_hint;
 }
-
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Workspace bytes of the rotary table of mlkv_decode_step_rope: (cos, sin)
 // in double for each sequence and channel pair.
@@ -727,6 +812,10 @@ size_t mlkv_workspace_bytes(const mlkv_map* map, int batch, int capacity, int he
     const size_t need = workspace_need(batch, map->h, head_dim, pl);
     best = need > best ? need : best;
   }
+  if (best > 0 && map->layers_per_group > 0) {
+    const size_t need = step_plan(map, batch, capacity, head_dim, SIZE_MAX).need;
+    best = need > best ? need : best;
+  }
   return best;
 }
 
@@ -917,8 +1006,58 @@ mlkv_status decode_step_check(const void* q_all, const void* k_new_all, const vo
   return MLKV_OK;
 }
 
-// The step's launches: per layer, the append it owns (when not fused) and
-// its attention.
+// The step in one launch (step.hip).
+mlkv_status step_launch(const void* q_all, const uint16_t* k_new, const uint16_t* v_new,
+                        const mlkv_cache* cache, const mlkv_map* map, const int32_t* ctx_lens,
+                        void* out_all, mlkv_out_dtype out_dtype, int max_len_hint, void* workspace,
+                        size_t workspace_bytes, hipStream_t stream, const double* rope_cs,
+                        int rope_half) {
+  const int B = cache->batch, D = cache->head_dim;
+  const int max_len = max_len_of(cache, max_len_hint);
+  const StepPlan pl = step_plan(map, B, max_len, D, workspace ? workspace_bytes : 0);
+  char* base = static_cast<char*>(workspace);
+  mlkv::StepParams p{};
+  p.q = static_cast<const uint16_t*>(q_all);
+  p.k = static_cast<const uint16_t*>(cache->k);
+  p.v = static_cast<const uint16_t*>(cache->v);
+  p.k_new = k_new;
+  p.v_new = v_new;
+  p.ctx = ctx_lens;
+  p.out = out_all;
+  if (pl.runs > 1) {
+    p.counters = reinterpret_cast<int*>(base);
+    p.part_acc = reinterpret_cast<float*>(base + kCounterSlots * sizeof(int32_t));
+    p.part_ml = reinterpret_cast<float*>(base + pl.ml);
+  }
+  p.rope_cs = rope_half > 0 ? rope_cs : nullptr;
+  p.rope_half = rope_half > 0 ? rope_half : 0;
+  p.B = B;
+  p.h = map->h;
+  p.S = cache->capacity;
+  p.n_kv = map->n_kv;
+  p.layers = map->layers_per_group;
+  p.kv_per_layer = map->kv_count[0];
+  p.G = map->group[0];
+  p.chunks = pl.chunks;
+  p.chunk_rows = pl.chunk_rows;
+  p.runs = pl.runs;
+  p.waves = pl.waves;
+  p.min_tiles = kMinTiles;
+  p.items = static_cast<unsigned>(pl.units * pl.runs);
+  p.max_len = max_len;
+  p.out_bf16 = out_dtype == MLKV_OUT_BF16 ? 1 : 0;
+  p.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
+  Profile& prof = g_profile;
+  const bool timed = prof.on && prof.used < static_cast<int>(prof.start.size());
+  const hipError_t err = mlkv::launch_step(p, D, stream, timed ? prof.start[prof.used] : nullptr,
+                                           timed ? prof.stop[prof.used] : nullptr);
+  if (err != hipSuccess) return fail(MLKV_ERR_HIP, "step launch: %s", hipGetErrorString(err));
+  if (timed) ++prof.used;
+  return ok();
+}
+
+// The step's launches: one for all layers where the map allows, else per
+// layer the append it owns (when not fused) and its attention.
 mlkv_status decode_step_launch(const void* q_all, const void* k_new_all, const void* v_new_all,
                                const mlkv_cache* cache, const mlkv_map* map,
                                const int32_t* ctx_lens, void* out_all, mlkv_out_dtype out_dtype,
@@ -931,6 +1070,9 @@ mlkv_status decode_step_launch(const void* q_all, const void* k_new_all, const v
   const size_t out_elem_bytes = out_dtype == MLKV_OUT_BF16 ? 2 : 4;
   const uint16_t* k_new = static_cast<const uint16_t*>(k_new_all);
   const uint16_t* v_new = static_cast<const uint16_t*>(v_new_all);
+  if (step_in_one_launch(map, B, D))
+    return step_launch(q_all, k_new, v_new, cache, map, ctx_lens, out_all, out_dtype, max_len_hint,
+                       workspace, workspace_bytes, stream, rope_cs, rope_half);
   PlanKey planned_key;
   for (int n = 0; n < map->l; ++n) {
     // The attention launch appends the heads the layer owns when it reads

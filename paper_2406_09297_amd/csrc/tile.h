@@ -113,6 +113,30 @@ struct WaveState {
 // skip rescaling the accumulators.  Any reference gives the same softmax.
 constexpr float kLazyRescale = 8.f;
 
+// The newest token (position pos_new of the tile at t0) takes its key and
+// value from new_row (LDS: key then value, D each).
+template <int D>
+__device__ __forceinline__ void take_new_row(Tile<D>& t, int t0, int col, int grp, int pos_new,
+                                             const uint16_t* new_row) {
+  constexpr int KK = Tile<D>::KK, DB = Tile<D>::DB;
+#pragma unroll
+  for (int sb = 0; sb < 2; ++sb) {
+    if (t0 + (col >> 2) * 8 + sb * 4 + (col & 3) == pos_new) {
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+        t.k[sb][kk] = *reinterpret_cast<const u16x8*>(new_row + grp * 8 + kk * 32);
+    }
+  }
+  const int e_new = pos_new - t0 - grp * 8;  // in [0, 8) for the lanes holding it
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+    const uint16_t vn = new_row[D + db * 16 + col];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (e == e_new) t.v[db][e] = vn;
+  }
+}
+
 // LAST: the wave's last tile of its run, the only one that can hold the
 // ragged end of a sequence or the newest token.  pos_new >= 0: position of
 // the newest token, whose key and value are taken from new_row (LDS: key
@@ -122,24 +146,8 @@ __device__ __forceinline__ void process_tile(WaveState<D>& st, Tile<D>& t, const
                                              int t0, int L, int col, int grp, float scale_log2,
                                              int pos_new, const uint16_t* new_row) {
   constexpr int KK = Tile<D>::KK, DB = Tile<D>::DB;
-  if (LAST && pos_new >= t0 && pos_new < t0 + kTile) {
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
-      if (t0 + (col >> 2) * 8 + sb * 4 + (col & 3) == pos_new) {
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-          t.k[sb][kk] = *reinterpret_cast<const u16x8*>(new_row + grp * 8 + kk * 32);
-      }
-    }
-    const int e_new = pos_new - t0 - grp * 8;  // in [0, 8) for the lanes holding it
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const uint16_t vn = new_row[D + db * 16 + col];
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (e == e_new) t.v[db][e] = vn;
-    }
-  }
+  if (LAST && pos_new >= t0 && pos_new < t0 + kTile)
+    take_new_row<D>(t, t0, col, grp, pos_new, new_row);
   float x[8];  // raw scores q.k of tokens 8*grp + e
   {
     f32x4 s[2];

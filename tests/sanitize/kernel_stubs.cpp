@@ -33,6 +33,9 @@ hipError_t launch_attention_main(const AttnParams&, int, hipStream_t, hipEvent_t
 hipError_t launch_attention_merge(const AttnParams&, int, hipStream_t, hipEvent_t) {
   return no_device();
 }
+hipError_t launch_step(const StepParams&, int, hipStream_t, hipEvent_t, hipEvent_t) {
+  return no_device();
+}
 hipError_t launch_fill(uint32_t*, size_t, uint32_t, hipStream_t) { return no_device(); }
 hipError_t launch_empty_timed(int, int, hipStream_t, hipEvent_t, hipEvent_t) { return no_device(); }
 hipError_t launch_stream_read_timed(const void*, size_t, uint32_t*, int, hipStream_t, hipEvent_t,

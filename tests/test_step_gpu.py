@@ -1,0 +1,158 @@
+"""The decode step in one launch (csrc/step.hip) against the fp64 oracle and
+against the layer-by-layer launches, at the edges of its plan: one to three
+blocks of query rows, rows in several chunks, split and whole units, four- and
+eight-wave workgroups, and maps given as tables."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+from gpu_util import DeviceWorkload, check_close, say, step_rounding_bound  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+mlkv = pytest.importorskip("paper_2406_09297_amd")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    mlkv.lib()
+    yield
+
+
+def _lengths(B, top):
+    """Contexts around tile edges, an empty sequence, the longest."""
+    base = [min(x, top) for x in (-1, 0, 30, 31, 32, 33, 63, 64, top)]
+    return np.array([base[i % len(base)] if i < len(base) else (i * 37) % (top + 1)
+                     for i in range(B)], np.int32)
+
+
+def _step(dw, out_dtype=torch.float32, ws=None, rd=0):
+    w = dw.w
+    out = torch.full((w.l, w.B, w.h, w.D), float("nan"), dtype=out_dtype, device="cuda")
+    mlkv.decode_step(dw.q, dw.k_new, dw.v_new, dw.cache, dw.map, dw.ctx, out,
+                     ws=dw.ws if ws is None else ws, rotary_dims=rd)
+    torch.cuda.synchronize()
+    return out.float().cpu().numpy()
+
+
+def _prepare(l, h, m, g, D, B, top, seed):
+    w = synth.Workload("one_launch", l=l, h=h, m=m, g=g, D=D, B=B, ctx=top, seed=seed)
+    dw = DeviceWorkload(w)
+    ctx = _lengths(B, top)
+    dw.host["ctx"] = ctx
+    dw.ctx = torch.from_numpy(ctx).cuda()
+    return dw
+
+
+def _check(dw, tag):
+    out = _step(dw)
+    again = _step(dw)
+    assert np.array_equal(out, again), f"{tag}: a repeated step differs"
+    k_gpu, v_gpu = dw.read_cache()
+    k, v = dw.host["k_cache"].copy(), dw.host["v_cache"].copy()
+    ref = oracle.decode_step(dw.host["q"], k, v, dw.host["k_new"], dw.host["v_new"], dw.kv_of,
+                             dw.owner_of, dw.host["ctx"])
+    assert np.array_equal(k_gpu, k) and np.array_equal(v_gpu, v), f"{tag}: cache differs"
+    check_close(out, ref, tag, bound=step_rounding_bound(dw.host["q"], k, v, dw.kv_of,
+                                                         dw.host["ctx"], ref))
+    return out
+
+
+@pytest.mark.parametrize("l,h,m,g,D,B,top", [
+    (4, 4, 2, 4, 64, 9, 70),       # two rows per KV head; whole units
+    (4, 8, 2, 1, 64, 9, 700),      # sixteen rows: one full block; split runs
+    (4, 9, 2, 1, 64, 9, 900),      # eighteen rows: two blocks, the second nearly empty
+    (6, 12, 2, 1, 64, 9, 1300),    # thirty-six rows in two chunks, split runs
+    (12, 12, 1, 1, 64, 2, 2047),   # 144 rows in five chunks, most runs per unit
+    (6, 12, 2, 1, 64, 130, 95),    # 260 units: three blocks on four-wave workgroups
+    (12, 12, 1, 1, 64, 60, 95),    # 60 units x 144 rows: three chunks of three blocks
+    (4, 2, 4, 2, 64, 100, 40),     # 800 units: eight waves, whole units
+    (4, 8, 2, 2, 128, 9, 500),     # head dim 128, eight rows
+    (8, 8, 1, 2, 128, 3, 1500),    # 32 rows in two chunks, split runs
+    (8, 8, 1, 2, 128, 150, 40),    # 300 units: two blocks on four-wave workgroups
+    (8, 16, 1, 1, 128, 40, 70),    # 128 rows: four chunks of two blocks
+])
+def test_one_launch_step_matches_oracle(l, h, m, g, D, B, top):
+    tag = f"one launch l{l} h{h} m{m} g{g} D{D} B{B} top{top}"
+    say(tag)
+    _check(_prepare(l, h, m, g, D, B, top, seed=31 + l + h), tag)
+
+
+@pytest.mark.parametrize("kv_of,owner_of", [
+    ([[0] * 4, [0] * 4, [1] * 4, [1] * 4], [0, 2]),              # equal groups: one launch
+    ([[0, 0, 1, 1], [2, 2, 3, 3]], [0, 0, 1, 1]),                # no sharing across layers
+    ([[0] * 4, [0] * 4, [0] * 4, [1] * 4], [0, 3]),              # groups of different sizes
+    ([[0] * 4, [1] * 4, [0] * 4, [1] * 4], [0, 1]),              # groups interleaved
+    ([[0, 0, 1, 1], [0, 0, 1, 1], [2] * 4, [2] * 4], [0, 0, 2]),  # head counts differ
+    ([[0, 0, 1, 1], [1] * 4], [0, 0]),                           # a layer reading half a group
+])
+def test_table_maps_match_oracle_and_layer_by_layer(kv_of, owner_of, monkeypatch):
+    """Maps that do and do not fall into equal groups of layers: the oracle
+    decides, and the layer-by-layer launches (any override of the per-layer
+    plan selects them) leave the same cache and outputs within the rounding
+    of the softmax weights."""
+    kv_of, owner_of = np.array(kv_of, np.int32), np.array(owner_of, np.int32)
+    l, n_kv = kv_of.shape[0], owner_of.size
+    w = synth.Workload("tables", l=l, h=4, m=n_kv, g=1, D=64, B=9, ctx=330, seed=77) \
+        if l % n_kv == 0 else synth.Workload("tables", l=n_kv * l, h=4, m=n_kv, g=1, D=64, B=9,
+                                             ctx=330, seed=77)
+    dw = DeviceWorkload(w)
+    if w.l != l:  # the generator's layers beyond the map's are not used
+        dw.host["q"] = np.ascontiguousarray(dw.host["q"][:l])
+        dw.q = mlkv.bf16_tensor(dw.host["q"], "cuda")
+        dw.w = synth.Workload("tables", l=l, h=4, m=n_kv, g=1, D=64, B=9, ctx=330, seed=77)
+    ctx = _lengths(9, 330)
+    dw.host["ctx"], dw.ctx = ctx, torch.from_numpy(ctx).cuda()
+    dw.map = mlkv.Map.from_tables(kv_of, owner_of)
+    dw.kv_of, dw.owner_of = kv_of, owner_of
+    dw.ws = mlkv.workspace(dw.map, 9, dw.S, 64)
+    tag = f"tables {kv_of.tolist()}"
+    say(tag)
+    out = _check(dw, tag)
+    monkeypatch.setenv("MLKV_WORKGROUPS", "512")
+    layers = _step(dw)
+    # Both are within the oracle's bound; each weight is rounded to bf16
+    # (2^-8 relative) against references that may differ.
+    assert np.max(np.abs(out - layers)) <= 2.0 ** -7 * max(1.0, np.abs(layers).max())
+
+
+def test_small_workspace_and_bf16_and_rotation():
+    """A workspace that holds the layer-by-layer step's needs but not every
+    run of the one-launch plan is accepted and gives fewer runs; bf16 outputs
+    are the rounded fp32 ones; the rotated step leaves rotated keys."""
+    dw = _prepare(12, 12, 4, 1, 64, 2, 2000, seed=5)
+    say("one launch: workspaces, bf16, rotation")
+    full = _step(dw)
+    counters = 65536 * 4
+    per_layer = 0
+    for n in range(12):  # the documented layout of the layer-by-layer plan
+        wg, parts = dw.map.plan(n, 2, dw.S, 64, dw.S)
+        rows = 2 * 12 * parts
+        up = lambda x: -(-x // 256) * 256  # noqa: E731
+        per_layer = max(per_layer, counters + up(8) + up(wg * 32) + up(rows * 64 * 4) + rows * 8)
+    tight = dw.ws[:per_layer].clone().zero_()
+    out = _step(dw, ws=tight)
+    k_gpu, v_gpu = dw.read_cache()
+    k, v = dw.host["k_cache"].copy(), dw.host["v_cache"].copy()
+    ref = oracle.decode_step(dw.host["q"], k, v, dw.host["k_new"], dw.host["v_new"], dw.kv_of,
+                             dw.owner_of, dw.host["ctx"])
+    assert np.array_equal(k_gpu, k) and np.array_equal(v_gpu, v)
+    bound = step_rounding_bound(dw.host["q"], k, v, dw.kv_of, dw.host["ctx"], ref)
+    check_close(out, ref, "tight workspace", bound=bound)
+    check_close(full, ref, "full workspace", bound=bound)
+    with pytest.raises(mlkv.MLKVError):
+        _step(dw, ws=dw.ws[:counters // 2].clone())
+    half = _step(dw, out_dtype=torch.bfloat16)
+    assert np.array_equal(synth.f32_to_bf16(half), synth.f32_to_bf16(full))
+    ws = mlkv.workspace(dw.map, 2, dw.S, 64, rotary_dims=16)
+    _step(dw, ws=ws, rd=16)
+    k_gpu, _ = dw.read_cache()
+    k = dw.host["k_cache"].copy()
+    oracle.decode_step_rope(dw.host["q"], k, v, dw.host["k_new"], dw.host["v_new"], dw.kv_of,
+                            dw.owner_of, dw.host["ctx"], 16, 10000.0)
+    assert np.array_equal(k_gpu, k)
