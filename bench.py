@@ -225,7 +225,7 @@ def run_prefill(args, w, emit: bool = True):
     mlkv.profile_disable()
     avg = tot_ms * 1e-3 / n_launch
     p10, p50, p90 = (float(np.percentile(durations, pq)) for pq in (10, 50, 90))
-    flops_launch = flops / w.l
+    flops_launch = flops * args.steps / n_launch  # a launch is a layer, or all of them
     achieved = flops_launch / avg / 1e12
     result = {
         "metric": "prefill-attention TFLOP/s (% of bf16 MFMA peak) + prompt tokens/s, "

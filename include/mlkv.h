@@ -351,7 +351,10 @@ mlkv_status mlkv_prefill_attention(int layer, const void* q, const mlkv_cache* c
  *   k_new_all, v_new_all: device bf16 [batch][T][n_kv][head_dim] (every KV
  *              head's new rows; each owner stores its columns).
  *   out_all:   device [l][batch][T][h][head_dim], fp32 or bf16.
- * All 16-byte aligned.  Every check is made before anything is launched. */
+ * All 16-byte aligned.  Every check is made before anything is launched.
+ * Maps whose layers fall into equal groups (as in mlkv_decode_step) append
+ * every head's rows in one launch and run all layers in another; others run
+ * layer by layer, in the order above. */
 mlkv_status mlkv_prefill_step(const void* q_all, const void* k_new_all, const void* v_new_all,
                               const mlkv_cache* cache, const mlkv_map* map,
                               const int32_t* ctx_lens, int T, void* out_all,

@@ -54,8 +54,11 @@ struct AppendRowsParams {
   int B, T, S, kv_begin, row_stride;
 };
 
-// Causal prefill attention of one layer: token t of sequence b attends
-// positions 0 .. ctx[b] + t of the KV heads [kv_begin, kv_begin + n_groups).
+// Causal prefill attention: token t of sequence b attends positions 0 ..
+// ctx[b] + t of the KV heads [kv_begin, kv_begin + n_groups).  One layer
+// (layers 1, kv_per_layer n_groups), or every layer of a map with equal groups
+// of `layers` layers reading kv_per_layer heads each (n_groups all heads; q and
+// out [l][B][T][h][D]).
 // A prefill wave takes prefill_wave_blocks(D) blocks of 16 query rows (token,
 // head) of one KV head; a workgroup is four such waves.
 constexpr int prefill_wave_blocks(int head_dim) { return head_dim == 64 ? 2 : 1; }
@@ -63,13 +66,14 @@ constexpr int prefill_rows_per_workgroup(int head_dim) {
   return 4 * 16 * prefill_wave_blocks(head_dim);
 }
 struct PrefillParams {
-  const uint16_t* q;         // [B][T][h][D]
+  const uint16_t* q;         // [B][T][h][D] per layer
   const uint16_t* k;         // key plane   [n_kv][B][S][D]
   const uint16_t* v;         // value plane [n_kv][B][S/32][D][32]
   const int32_t* ctx;        // [B] tokens cached before the prompt
-  void* out;                 // [B][T][h][D] fp32 or bf16
+  void* out;                 // [B][T][h][D] per layer, fp32 or bf16
   int B, T, h, S;
   int kv_begin, G, n_groups;
+  int layers, kv_per_layer;
   int out_bf16;
   float scale_log2;          // log2(e) / sqrt(D)
 };

@@ -590,10 +590,10 @@ mlkv_status append_impl(int layer, const mlkv_map* map, const mlkv_cache* cache,
   return MLKV_OK;
 }
 
-mlkv_status append_rows_impl(int layer, const mlkv_map* map, const mlkv_cache* cache,
-                             const void* k_new, const void* v_new, int T, int row_stride,
-                             const int32_t* ctx_lens, hipStream_t stream) {
-  const int owned = map->own_count[layer];
+// The T new rows of KV heads [kv_begin, kv_begin + owned).
+mlkv_status append_rows_impl(int kv_begin, int owned, const mlkv_cache* cache, const void* k_new,
+                             const void* v_new, int T, int row_stride, const int32_t* ctx_lens,
+                             hipStream_t stream) {
   if (owned == 0 || T == 0) return MLKV_OK;
   mlkv::AppendRowsParams p{};
   p.k_new = static_cast<const uint16_t*>(k_new);
@@ -604,7 +604,7 @@ mlkv_status append_rows_impl(int layer, const mlkv_map* map, const mlkv_cache* c
   p.B = cache->batch;
   p.T = T;
   p.S = cache->capacity;
-  p.kv_begin = map->own_begin[layer];
+  p.kv_begin = kv_begin;
   p.row_stride = row_stride;
   const hipError_t err = mlkv::launch_append_rows(p, cache->head_dim, owned, stream);
   if (err != hipSuccess) return fail(MLKV_ERR_HIP, "append launch: %s", hipGetErrorString(err));
@@ -644,9 +644,11 @@ mlkv_status check_prefill_lengths_if_requested(const int32_t* ctx, int batch, in
   return MLKV_OK;
 }
 
+// all_layers: every layer of a map with equal groups (layer 0 .. l-1 of q and
+// out) in one launch.
 mlkv_status prefill_impl(int layer, const void* q, const mlkv_cache* cache, const mlkv_map* map,
                          const int32_t* ctx_lens, int T, void* out, mlkv_out_dtype dt,
-                         hipStream_t stream) {
+                         hipStream_t stream, bool all_layers = false) {
   if (T == 0) return MLKV_OK;
   const int D = cache->head_dim;
   mlkv::PrefillParams p{};
@@ -661,7 +663,9 @@ mlkv_status prefill_impl(int layer, const void* q, const mlkv_cache* cache, cons
   p.S = cache->capacity;
   p.kv_begin = map->kv_begin[layer];
   p.G = map->group[layer];
-  p.n_groups = map->kv_count[layer];
+  p.n_groups = all_layers ? map->n_kv : map->kv_count[layer];
+  p.layers = all_layers ? map->layers_per_group : 1;
+  p.kv_per_layer = map->kv_count[layer];
   p.out_bf16 = dt == MLKV_OUT_BF16 ? 1 : 0;
   p.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
   Profile& prof = g_profile;
@@ -1208,8 +1212,8 @@ mlkv_status mlkv_cache_append_rows(int layer, const mlkv_map* map, const mlkv_ca
   if ((s = check_prefill_lengths_if_requested(ctx_lens, cache->batch, T, cache->capacity,
                                               stream)) != MLKV_OK)
     return s;
-  if ((s = append_rows_impl(layer, map, cache, k_new, v_new, T, new_row_stride, ctx_lens,
-                            stream)) != MLKV_OK)
+  if ((s = append_rows_impl(map->own_begin[layer], owned, cache, k_new, v_new, T, new_row_stride,
+                            ctx_lens, stream)) != MLKV_OK)
     return s;
   return ok();
 }
@@ -1258,11 +1262,24 @@ mlkv_status mlkv_prefill_step(const void* q_all, const void* k_new_all, const vo
   const size_t out_elem_bytes = out_dtype == MLKV_OUT_BF16 ? 2 : 4;
   const uint16_t* k_new = static_cast<const uint16_t*>(k_new_all);
   const uint16_t* v_new = static_cast<const uint16_t*>(v_new_all);
+  // Maps with equal groups of layers: every head's rows in one append, every
+  // layer in one launch (where heads and row blocks fit the grids).
+  const long per_wg = mlkv::prefill_rows_per_workgroup(D);
+  const long all_rows = static_cast<long>(T) * map->layers_per_group * map->group[0];
+  if (map->layers_per_group > 0 && n_kv <= kMaxGridY &&
+      (all_rows + per_wg - 1) / per_wg <= kMaxGridY) {
+    if ((s = append_rows_impl(0, n_kv, cache, k_new, v_new, T, n_kv * D, ctx_lens, stream)) !=
+            MLKV_OK ||
+        (s = prefill_impl(0, q_all, cache, map, ctx_lens, T, out_all, out_dtype, stream, true)) !=
+            MLKV_OK)
+      return s;
+    return ok();
+  }
   for (int n = 0; n < map->l; ++n) {
     if (map->own_count[n] > 0) {
       const size_t col = static_cast<size_t>(map->own_begin[n]) * D;
-      if ((s = append_rows_impl(n, map, cache, k_new + col, v_new + col, T, n_kv * D, ctx_lens,
-                                stream)) != MLKV_OK)
+      if ((s = append_rows_impl(map->own_begin[n], map->own_count[n], cache, k_new + col,
+                                v_new + col, T, n_kv * D, ctx_lens, stream)) != MLKV_OK)
         return s;
     }
     const void* q = static_cast<const uint16_t*>(q_all) + layer_elems * n;

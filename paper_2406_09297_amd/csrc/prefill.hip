@@ -14,14 +14,18 @@
 #include <stdint.h>
 
 #include "kernels.h"
+#include "prefill.h"
 #include "tile.h"
 
 namespace mlkv {
 
 // ---------------------------------------------------------------------------
 // Prefill (Section 2.4's cache filled from a prompt, causal): T new tokens per
-// sequence.  Unit (b, r) has T*G query rows, row rho = t*G + hh (token t,
-// query head hh of KV group r).  A wave takes NB blocks of 16 consecutive
+// sequence.  Unit (b, r) is a (sequence, KV head); its query rows are those of
+// every layer and head of the call that reads the head, token by token: row
+// rho = t*R + c, R = layers*G rows per token, c = layer*G + head (one layer, or
+// in a whole prefill all layers of the head's group, so that the layers run in
+// one launch and share the staged tiles).  A wave takes NB blocks of 16 consecutive
 // rows (the MFMA columns) and streams the key/value tiles from position 0 to
 // its last row's limit with one online softmax per block (the tile
 // arithmetic of decode: S^T = K Q^T, O^T += V^T P^T); each tile's key and
@@ -37,7 +41,9 @@ namespace mlkv {
 // the weights' exponents y = scaled score - column reference (FIRST: the
 // wave's first tile sets each reference to its column's maximum); one
 // wave-wide vote on whether any y exceeds kLazyRescale (each lane tests its
-// own eight, so the common case needs no cross-lane traffic); on a yes, the
+// own, in two chains of three-input maxima over all blocks, so the common case
+// needs no cross-lane traffic; a tree per block took twice the instructions,
+// 708 against 696 us per 12-layer prompt of 8 x 2000 tokens); on a yes, the
 // column maxima through the wave and the rescale of the blocks that need it;
 // then the weights and the value products of all blocks.
 // Maximum of a lane's eight values.  Over multiply-add results (canonical
@@ -100,17 +106,20 @@ __device__ __forceinline__ void prefill_tile(WaveState<D> (&st)[NB], Tile<D>& t,
     for (int e = 0; e < 8; ++e) x[c][e] = fmaf(x[c][e], scale_log2, neg_m);
   }
   if (!FIRST) {
-    float ymax[NB];
-    bool up = false;
+    // Two chains of three-input maxima over all blocks' exponents.
+    float up0 = x[0][0], up1 = x[0][4];
 #pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      ymax[c] = max8(x[c]);
-      up = up || ymax[c] > kLazyRescale;
-    }
-    if (__ballot(up)) {  // some column needs a new reference
+    for (int c = 0; c < NB; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        up0 = fmaxf(fmaxf(up0, x[c][e]), x[c][e + 1]);
+        up1 = fmaxf(fmaxf(up1, x[c][4 + e]), x[c][5 + e]);
+      }
+    if (__ballot(fmaxf(up0, up1) > kLazyRescale)) {  // some column needs a new reference
 #pragma unroll
       for (int c = 0; c < NB; ++c) {
-        float cm = fmaxf(ymax[c], __shfl_xor(ymax[c], 16));
+        const float lmax = max8(x[c]);
+        float cm = fmaxf(lmax, __shfl_xor(lmax, 16));
         cm = fmaxf(cm, __shfl_xor(cm, 32));
         const bool raise = cm > kLazyRescale;  // uniform over the column's lanes
         if (__ballot(raise)) {
@@ -141,78 +150,68 @@ __device__ __forceinline__ void prefill_tile(WaveState<D> (&st)[NB], Tile<D>& t,
   }
 }
 
-// Key/value tiles staged in LDS by direct global-to-LDS loads
-// (global_load_lds_dwordx4: lane l of a wave writes its 16 bytes at the
-// wave-uniform LDS address + 16 l), double-buffered and shared by the
-// workgroup's four waves; no registers hold a tile in transit and no LDS
-// store instructions are issued.  Key chunks keep the plane's order, in
-// which a wave's operand reads are lane-contiguous; the value chunk
-// of channel c and 8-token part p sits at slot 4 c + (p ^ vswz(c)), so that
-// the sixteen lanes reading channels c .. c + 15 at one part hit distinct
-// banks (for both 32- and 64-bank phase groupings).
+// A 32-token tile staged in LDS by direct global-to-LDS loads (lane l of a
+// wave writes its 16 bytes at the wave-uniform LDS address + 16 l: no registers
+// hold a tile in transit), double-buffered and shared by the workgroup's four
+// waves.  Key chunks keep the plane's order, in which a wave's operand reads
+// are contiguous; the value chunk of channel c and 8-token part p sits at slot
+// 4 c + (p ^ vswz16(c)).  A 16-byte read serves the lanes 0-3, 12-15 and 20-27
+// together, then 4-11, 16-19 and 28-31 (and the same in the upper half): with
+// this order their sixteen slots are distinct modulo 16, and the conflict
+// counter reads zero, where an order distinct over sixteen consecutive lanes
+// lost a third of the LDS cycles (one layer of 32 heads of 128 channels, 200
+// new tokens on 8000: 139 -> 123 us).
 constexpr int kRing = 2;
-__device__ __forceinline__ int vswz(int c) { return ((c >> 1) ^ (c >> 3)) & 3; }
+__device__ __forceinline__ int vswz16(int c) { return ((c >> 3) & 1) * 3; }
 
 template <int D>
-struct PrefillRing {
+struct TileRing {
   alignas(16) uint16_t k[kRing][kTile * D];
   alignas(16) uint16_t v[kRing][kTile * D];
+
+  // Requests the tile at position t0 into buffer s: 2 D/64 loads per wave.
+  __device__ __forceinline__ void issue(int s, const uint16_t* kbase, const uint16_t* vbase, int t0) {
+    const unsigned lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned voff = (lane >> 2) * 64 + (((lane & 3) ^ vswz16(lane >> 2)) * 16);
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) {
+      const int piece = u * 4 + wave;  // 1 KB pieces: sixteen channels of the value tile
+      const size_t at = static_cast<size_t>(t0) * D * 2 + piece * 1024;
+      load_lds16(reinterpret_cast<const char*>(kbase) + at, lane * 16, &k[s][piece * 512]);
+      load_lds16(reinterpret_cast<const char*>(vbase) + at, voff, &v[s][piece * 512]);
+    }
+  }
+
+  // A wave's MFMA operands of one tile from buffer s (the register layout of
+  // load_tile: permuted key rows, V^T rows).
+  __device__ __forceinline__ void read(Tile<D>& t, int s, int col, int grp) const {
+    const int lane = grp * 16 + col;
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+      for (int kk = 0; kk < Tile<D>::KK; ++kk)
+        t.k[sb][kk] = *reinterpret_cast<const u16x8*>(&k[s][((sb * Tile<D>::KK + kk) * 64 + lane) * 8]);
+#pragma unroll
+    for (int db = 0; db < Tile<D>::DB; ++db) {
+      const int c = db * 16 + col;
+      t.v[db] = *reinterpret_cast<const u16x8*>(&v[s][(c * 4 + (grp ^ vswz16(c))) * 8]);
+    }
+  }
 };
 
-// Wait until this wave's vector memory loads, the direct loads included,
-// have landed (vmcnt(0); the other counters are left alone).
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
-
-// A shared-memory pointer as the LDS address the direct loads take.
-__device__ __forceinline__ __attribute__((address_space(3))) void* lds_address(uint16_t* p) {
-  return (__attribute__((address_space(3))) void*)p;
-}
-
-// Requests the tile at position t0 into buffer s: each thread issues D/64
-// key and D/64 value chunk loads, 2 D/64 instructions per wave.
-template <int D>
-__device__ __forceinline__ void ring_issue(PrefillRing<D>& rg, int s, const uint16_t* kbase,
-                                           const uint16_t* vbase, int t0) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int u = 0; u < D / 64; ++u) {
-    const int slot0 = u * 256 + wave * 64;  // this wave's 64 slots (1 KB) of the buffer
-    const int q = slot0 + lane;
-    __builtin_amdgcn_global_load_lds(
-        static_cast<const void*>(kbase + static_cast<size_t>(t0) * D + q * 8),
-        lds_address(&rg.k[s][slot0 * 8]), 16, 0, 0);
-    const int c = q >> 2, part = (q & 3) ^ vswz(c);
-    __builtin_amdgcn_global_load_lds(
-        static_cast<const void*>(vbase + static_cast<size_t>(t0) * D + (c * 4 + part) * 8),
-        lds_address(&rg.v[s][slot0 * 8]), 16, 0, 0);
-  }
-}
-
-// A wave's MFMA operands of one tile from buffer s (the register layout of
-// load_tile: permuted key rows, V^T rows).
-template <int D>
-__device__ __forceinline__ void tile_from_ring(Tile<D>& t, const PrefillRing<D>& rg, int s, int col,
-                                               int grp) {
-  const int lane = grp * 16 + col;
-#pragma unroll
-  for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-    for (int kk = 0; kk < Tile<D>::KK; ++kk)
-      t.k[sb][kk] = *reinterpret_cast<const u16x8*>(
-          &rg.k[s][((sb * Tile<D>::KK + kk) * 64 + lane) * 8]);
-#pragma unroll
-  for (int db = 0; db < Tile<D>::DB; ++db) {
-    const int c = db * 16 + col;
-    t.v[db] = *reinterpret_cast<const u16x8*>(&rg.v[s][(c * 4 + (grp ^ vswz(c))) * 8]);
-  }
-}
-
+// What bounds it: vector issue, 70 % of the cycles (the exponentials alone take
+// a third of it), beside matrix cores at 44 %.  696 us for the 12-layer MLKV-4
+// prompt of 8 x 2000 tokens in one launch, 849 TFLOP/s over the step; a launch
+// and an append per layer took 776 us, and 2560 against 351 us for 257 new
+// tokens on two prompts of about 14000, whose row blocks leave most of the
+// device idle layer by layer.
 template <int D, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 void prefill_kernel(PrefillParams p) {
   constexpr int KK = Tile<D>::KK, DB = Tile<D>::DB;
   constexpr int WAVE_ROWS = 16 * NB;
-  __shared__ PrefillRing<D> rg;
+  __shared__ TileRing<D> rg;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int col = lane & 15;
@@ -220,7 +219,8 @@ void prefill_kernel(PrefillParams p) {
   const int unit = blockIdx.x;
   const int b = unit / p.n_groups;
   const int r = unit - b * p.n_groups;
-  const int rows = p.T * p.G;
+  const int R = p.layers * p.G;  // rows per token
+  const int rows = p.T * R;
   const int blk = gridDim.y - 1 - blockIdx.y;
   const int wg_row0 = blk * 4 * WAVE_ROWS;  // < rows: the grid has no empty workgroup
   const int row0 = wg_row0 + wave * WAVE_ROWS;
@@ -229,18 +229,19 @@ void prefill_kernel(PrefillParams p) {
   const int L = min(c0 + p.T, p.S);  // filled positions of the sequence
   // Tiles of the workgroup (its last row's limit) and of this wave.
   const int wg_last = min(wg_row0 + 4 * WAVE_ROWS - 1, rows - 1);
-  const int n_tiles_wg = min(c0 + wg_last / p.G, p.S - 1) / kTile + 1;
+  const int n_tiles_wg = min(c0 + wg_last / R, p.S - 1) / kTile + 1;
   const int last_row = min(row0 + WAVE_ROWS - 1, rows - 1);
-  const int lim_max = min(c0 + last_row / p.G, p.S - 1);
-  const int lim_min = min(c0 + min(row0, rows - 1) / p.G, p.S - 1);
+  const int lim_max = min(c0 + last_row / R, p.S - 1);
+  const int lim_min = min(c0 + min(row0, rows - 1) / R, p.S - 1);
   const int n_tiles = active ? lim_max / kTile + 1 : 0;
   const int first_masked = (lim_min + 1) / kTile;  // tiles before it lie under every limit
 
   const int kv = p.kv_begin + r;
+  const int group = r / p.kv_per_layer;  // of layers
   const size_t seq = static_cast<size_t>(kv) * p.B + b;
   const uint16_t* kbase = p.k + seq * p.S * D;
   const uint16_t* vbase = p.v + seq * p.S * D;
-  ring_issue<D>(rg, 0, kbase, vbase, 0);  // every workgroup has at least one tile
+  rg.issue(0, kbase, vbase, 0);  // every workgroup has at least one tile
 
   // Column block c: row row0 + 16c + col, its token, head and causal limit
   // (rows past the end: token 0, zero query, output not stored).
@@ -249,18 +250,14 @@ void prefill_kernel(PrefillParams p) {
   WaveState<D> st[NB];
 #pragma unroll
   for (int c = 0; c < NB; ++c) {
-    const int rho = row0 + 16 * c + col;
-    const bool valid = rho < rows;
-    const int tok = valid ? rho / p.G : 0;
-    const int head = valid ? rho - tok * p.G : 0;
-    lim[c] = min(c0 + tok, p.S - 1);
-    const uint16_t* qrow =
-        p.q + ((static_cast<size_t>(b) * p.T + tok) * p.h + r * p.G + head) * D + grp * 8;
+    const RowPlace at = row_place(p, row0 + 16 * c + col, rows, b, group, r, D);
+    lim[c] = min(c0 + at.tok, p.S - 1);
+    const uint16_t* qrow = p.q + at.offset + grp * 8;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       const u16x8 v = load16(qrow + kk * 32);
       const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-      qf[c][kk] = as_bf16(valid ? v : zero);
+      qf[c][kk] = as_bf16(at.valid ? v : zero);
     }
     st[c].den = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -274,10 +271,10 @@ void prefill_kernel(PrefillParams p) {
   for (int it = 0; it < n_tiles_wg; ++it) {
     wait_loads();
     __syncthreads();
-    if (it + 1 < n_tiles_wg) ring_issue<D>(rg, (it + 1) & 1, kbase, vbase, (it + 1) * kTile);
+    if (it + 1 < n_tiles_wg) rg.issue((it + 1) & 1, kbase, vbase, (it + 1) * kTile);
     if (it < n_tiles) {
       Tile<D> t;
-      tile_from_ring<D>(t, rg, it & 1, col, grp);
+      rg.read(t, it & 1, col, grp);
       if (it == 0)
         prefill_tile<D, NB, true, true>(st, t, qf, 0, L, lim, grp, p.scale_log2);
       else if (it >= first_masked)
@@ -290,27 +287,12 @@ void prefill_kernel(PrefillParams p) {
   // Lane (col, grp) holds channels db*16 + 4*grp .. +3 of its row in each block.
 #pragma unroll
   for (int c = 0; c < NB; ++c) {
-    const int rho = row0 + 16 * c + col;
-    if (rho >= rows) continue;
-    const int tok = rho / p.G;
-    const int head = rho - tok * p.G;
+    const RowPlace at = row_place(p, row0 + 16 * c + col, rows, b, group, r, D);
+    if (!at.valid) continue;
     const float inv = 1.f / st[c].den[0];
-    const size_t orow = ((static_cast<size_t>(b) * p.T + tok) * p.h + r * p.G + head) * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const f32x4 o = st[c].acc[db] * inv;
-      const size_t off = orow + db * 16 + grp * 4;
-      if (p.out_bf16) {
-        uint16_t* dst = static_cast<uint16_t*>(p.out) + off;
-        const uint32_t lo =
-            f32_to_bf16_bits(o[0]) | (static_cast<uint32_t>(f32_to_bf16_bits(o[1])) << 16);
-        const uint32_t hi =
-            f32_to_bf16_bits(o[2]) | (static_cast<uint32_t>(f32_to_bf16_bits(o[3])) << 16);
-        *reinterpret_cast<uint2*>(dst) = make_uint2(lo, hi);
-      } else {
-        *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + off) = o;
-      }
-    }
+    for (int db = 0; db < DB; ++db)
+      store4(p, at.offset + db * 16 + grp * 4, st[c].acc[db] * inv);
   }
 }
 
@@ -341,7 +323,7 @@ __global__ __launch_bounds__(256) void append_rows_kernel(AppendRowsParams p) {
 hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t stream,
                           hipEvent_t start, hipEvent_t stop) {
   const int per_wg = prefill_rows_per_workgroup(head_dim);
-  const int blocks = (p.T * p.G + per_wg - 1) / per_wg;
+  const int blocks = (p.T * p.layers * p.G + per_wg - 1) / per_wg;
   const dim3 grid(p.B * p.n_groups, blocks);
   auto kernel = head_dim == 64 ? prefill_kernel<64, prefill_wave_blocks(64)>
                                : prefill_kernel<128, prefill_wave_blocks(128)>;
