@@ -251,6 +251,13 @@ hipError_t launch_append_rows(const AppendRowsParams& p, int head_dim, int owned
 // start/stop: optional events recorded around the prefill dispatch.
 hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t stream,
                           hipEvent_t start, hipEvent_t stop);
+// Forms of prefill32.hip, called by launch_prefill where they are faster.
+constexpr int kPrefillWideRows = 256;  // query rows of a workgroup (head dim 128 only)
+constexpr int kPrefillSplitRows = 32;
+hipError_t launch_prefill_wide(const PrefillParams& p, hipStream_t stream, hipEvent_t start,
+                               hipEvent_t stop);
+hipError_t launch_prefill_split(const PrefillParams& p, int head_dim, hipStream_t stream,
+                                hipEvent_t start, hipEvent_t stop);
 // The split-K attention kernel, then (when splits are merged by a separate
 // kernel) the merge.
 // start/stop: optional events recorded around the attention dispatch.

@@ -1,6 +1,7 @@
 """The prefill's launches against the fp64 oracle where their shape changes:
 all layers in one launch (groups of layers sharing heads, several heads per
-layer, maps given as tables)."""
+layer, maps given as tables), the token-split form of small grids, 64- and
+256-row workgroups of head dim 128."""
 import numpy as np
 import pytest
 
@@ -36,3 +37,29 @@ def test_table_maps(kv_of, owner_of):
     tag = f"prefill tables {kv_of.tolist()}"
     say(tag)
     _check_case(PrefillCase(w, ctx=[3, 40], kv_of=kv_of, owner_of=owner_of), tag)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("T,ctx", [
+    (1, [0, 255]),     # one row block, fewer tiles than waves
+    (9, [223, 224]),   # last tile full and one past it
+    (40, [511, 3]),    # waves without a tile beside waves with several
+])
+def test_token_split_form(D, T, ctx):
+    w = synth.Workload("split", l=2, h=6, m=2, g=2, D=D, B=2, ctx=max(ctx), T=T, k_scale=3.0,
+                       seed=303)
+    tag = f"prefill split D{D} T{T} ctx{ctx}"
+    say(tag)
+    _check_case(PrefillCase(w, ctx=ctx), tag)
+
+
+@pytest.mark.parametrize("B,T,ctx", [
+    (10, 102, 0),    # 64-row workgroups, the last one ragged
+    (16, 130, 33),   # 256-row workgroups at two per compute unit, ragged, cached prefix
+    (17, 121, 0),
+])
+def test_head_dim_128_row_blocks(B, T, ctx):
+    w = synth.Workload("rows128", l=1, h=64, m=1, g=4, D=128, B=B, ctx=ctx, T=T, seed=304)
+    tag = f"prefill D128 B{B} T{T} ctx{ctx}"
+    say(tag)
+    _check_case(PrefillCase(w), tag)
