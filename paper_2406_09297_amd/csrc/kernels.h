@@ -215,13 +215,13 @@ struct PackParams {  // source W[k_rows][n_cols] row-major -> tiles (nt0 + nt, k
 struct LayerInParams {  // LN1/LN2 of x -> [q | k | v | fc1] products and their epilogues
   const float* x;                        // [rows][d] residual stream
   const uint16_t *ln1_w, *ln1_b, *ln2_w, *ln2_b;
-  const uint16_t* w;                     // packed, column blocks of D: h q, owned k, owned v, fc1
+  const uint16_t* w;                     // packed, columns of h q heads, owned k, owned v, fc1
   const uint16_t *b_q, *b_k, *b_v, *b_fc1;
   uint16_t* q16;                         // [rows][h*D]
   uint16_t *k16, *v16;                   // [rows][kv_stride], owned block at kv_offset
   uint16_t* f16;                         // [rows][ff], bf16(GELU(h2 W_1 + b_1))
   const int32_t* pos;                    // [rows] rotation position
-  int rows, d, h, owned, ff, kv_stride, kv_offset, dims;
+  int rows, d, h, D, owned, ff, kv_stride, kv_offset, dims;
   float eps;
   double inv_freq[kMaxRopePairs];
 };
@@ -234,7 +234,7 @@ struct LayerOutParams {  // x += (o W_o + b_o) + (f W_2 + b_2)
   const float* y_mlp;         // [rows][d] f W_2 + b_2 (SideProduct), or null: computed here
 };
 hipError_t launch_pack(const PackParams& p, hipStream_t stream);
-hipError_t launch_layer_in(const LayerInParams& p, int head_dim, hipStream_t stream);
+hipError_t launch_layer_in(const LayerInParams& p, hipStream_t stream);
 hipError_t launch_layer_out(const LayerOutParams& p, hipStream_t stream);
 
 hipError_t launch_norm2(const NormParams& p, hipStream_t stream);

@@ -1569,6 +1569,7 @@ mlkv_status mlkv_model_decode_step(mlkv_model* model, float* x, const mlkv_cache
       ip.rows = B;
       ip.d = d;
       ip.h = h;
+      ip.D = D;
       ip.owned = owned;
       ip.ff = ff;
       ip.kv_stride = kvD;
@@ -1576,7 +1577,7 @@ mlkv_status mlkv_model_decode_step(mlkv_model* model, float* x, const mlkv_cache
       ip.dims = model->dims;
       ip.eps = model->eps;
       std::memcpy(ip.inv_freq, model->inv_freq, sizeof ip.inv_freq);
-      if ((s = hip_ok(mlkv::launch_layer_in(ip, D, stream), "layer-in product")) != MLKV_OK)
+      if ((s = hip_ok(mlkv::launch_layer_in(ip, stream), "layer-in product")) != MLKV_OK)
         return s;
       // The MLP's second product rides in the attention launch (its extra
       // workgroups), leaving layer-out the W_o product and the sum.

@@ -181,33 +181,49 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// Column block blk of the layer-in product: q head blk (blk < h), then the
-// owned key heads, the owned value heads and the fc1 blocks, each D wide.
+// Column block blk of the layer-in product, 16 NT columns of [q heads | owned
+// key heads | owned value heads | fc1] (NT divides a head's 16-column tiles,
+// so a block lies inside one head), for 16 RT batch rows.
 // Each wave takes its k-blocks in chunks of PRE and issues every load of a
 // chunk (weights, the x rows, the layer-norm scale and shift) before the
 // first product, so a chunk costs one memory round trip; the first chunk's
 // loads are in flight while the layer-norm statistics are taken.
-template <int D>
+//
+// What bounds it: the round trips of a short launch and, at larger batches,
+// what one compute unit reads (at 128 rows of 768, 98 KB of weights and 98 KB
+// of x).  Whole-head blocks of 16 rows left 60 workgroups on 256 compute units
+// at small batches and ran two rounds at batch 128; statistics from a second
+// read of x cost it another 98 KB and ten shuffles a row.  12-layer step
+// (d 768, d_ff 3072), before and now: batch 8 236 -> 214 us, 128 455 -> 396.
+template <int NT, int RT>
 __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p) {
-  constexpr int NT = D / 16;
-  constexpr int PRE = 16 / NT;  // k-blocks per chunk: 4 (D = 64) or 2 (D = 128)
-  __shared__ f32x4 part[kFusedWaves][NT][64];
-  __shared__ float y[16][D + 1];
-  __shared__ float stats[16][2];
-  __shared__ double sc[16][kMaxRopePairs][2];
-  const int blk = blockIdx.x, b0 = blockIdx.y * 16;
+  constexpr int C = 16 * NT, R = 16 * RT;
+  constexpr int PRE = NT == 8 ? 2 : NT == 4 ? (RT == 1 ? 4 : 3) : RT == 1 ? 4 : 3;
+  __shared__ f32x4 part[kFusedWaves][RT][NT][64];
+  __shared__ float y[R][C + 1];
+  __shared__ float red[kFusedWaves][R];
+  __shared__ double sc[R][C / 2][2];  // a rotated block holds whole pairs
+  const int blk = blockIdx.x, b0 = blockIdx.y * R;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const bool mlp = blk >= p.h + 2 * p.owned;
+  // The head (or fc1 block of a head's width) the columns lie in, and where.
+  const int D = p.D, per_head = D / C;
+  const int head = blk / per_head, sub = (blk - head * per_head) * C;
+  const bool mlp = head >= p.h + 2 * p.owned;
   const uint16_t* lnw = mlp ? p.ln2_w : p.ln1_w;
   const uint16_t* lnb = mlp ? p.ln2_b : p.ln1_b;
   const int d = p.d, KB = d / 32;
   const int r = lane & 15, grp = lane >> 4;
-  const bool live = b0 + r < p.rows;
-  const float* xr = p.x + static_cast<size_t>(b0 + (live ? r : 0)) * d + 8 * grp;
+  bool live[RT];
+  const float* xr[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    live[t] = b0 + t * 16 + r < p.rows;
+    xr[t] = p.x + static_cast<size_t>(b0 + (live[t] ? t * 16 + r : 0)) * d + 8 * grp;
+  }
   const uint16_t* wblk = p.w + static_cast<size_t>(blk) * NT * KB * kPackTile + lane * 8;
 
   u16x8 a[PRE][NT], gw[PRE], gb[PRE];
-  float4 x0[PRE], x1[PRE];
+  float4 x0[PRE][RT], x1[PRE][RT];
   auto issue = [&](int base) {
 #pragma unroll
     for (int i = 0; i < PRE; ++i) {
@@ -216,11 +232,12 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
           a[i][nt] = load16(wblk + (static_cast<size_t>(nt) * KB + kb) * kPackTile);
-        if (live) {
-          x0[i] = *reinterpret_cast<const float4*>(xr + kb * 32);
-          x1[i] = *reinterpret_cast<const float4*>(xr + kb * 32 + 4);
-          gw[i] = load16(lnw + kb * 32 + 8 * grp);
-          gb[i] = load16(lnb + kb * 32 + 8 * grp);
+        gw[i] = load16(lnw + kb * 32 + 8 * grp);
+        gb[i] = load16(lnb + kb * 32 + 8 * grp);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          x0[i][t] = *reinterpret_cast<const float4*>(xr[t] + kb * 32);
+          x1[i][t] = *reinterpret_cast<const float4*>(xr[t] + kb * 32 + 4);
         }
       }
     }
@@ -228,35 +245,33 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
   issue(wave);
 
   const int half = p.dims / 2;
-  const int role = blk < p.h ? 0 : blk < p.h + p.owned ? 1 : blk < p.h + 2 * p.owned ? 2 : 3;
+  const int role = head < p.h ? 0 : head < p.h + p.owned ? 1 : head < p.h + 2 * p.owned ? 2 : 3;
+  // Rotated channels of this block: its first n_rot (none, or every one of
+  // the head's: the host takes blocks of at least `dims` columns).
+  const int n_rot = role < 2 && sub == 0 ? p.dims : 0;
   // The epilogue's biases (element e = threadIdx.x + k * kFusedThreads of the
-  // 16 x D tile: its own and, for rotated channels, its partner's), requested
+  // R x C tile: its own and, for rotated channels, its partner's), requested
   // now so that their latency hides under the products.
-  constexpr int kEpi = 16 * D / kFusedThreads;
+  constexpr int kEpi = (R * C + kFusedThreads - 1) / kFusedThreads;
   const uint16_t* const bias = role == 0 ? p.b_q : role == 1 ? p.b_k : role == 2 ? p.b_v : p.b_fc1;
-  const int jb = role == 0 ? blk : role == 1 ? blk - p.h : role == 2 ? blk - p.h - p.owned
-                                                                     : blk - p.h - 2 * p.owned;
+  const int jb = role == 0 ? head : role == 1 ? head - p.h : role == 2 ? head - p.h - p.owned
+                                                                       : head - p.h - 2 * p.owned;
+  const int col0 = jb * D + sub;  // the block's first column in its product
   float bias_own[kEpi], bias_partner[kEpi];
 #pragma unroll
   for (int k = 0; k < kEpi; ++k) {
-    const int e = threadIdx.x + k * kFusedThreads, rr = e / D, c = e % D;
+    const int e = threadIdx.x + k * kFusedThreads, rr = e / C, c = e % C;
     bias_own[k] = bias_partner[k] = 0.f;
-    if (b0 + rr >= p.rows) continue;
-    if (role == 3) {
-      if (jb * D + c < p.ff) bias_own[k] = bf16_to_f32(bias[jb * D + c]);
-      continue;
-    }
-    bias_own[k] = bf16_to_f32(bias[jb * D + c]);
-    if (role < 2 && c < p.dims) {
-      const int partner = c < half ? c + half : c - half;
-      bias_partner[k] = bf16_to_f32(bias[jb * D + partner]);
-    }
+    if (e >= R * C || b0 + rr >= p.rows) continue;
+    if (role == 3 && col0 + c >= p.ff) continue;
+    bias_own[k] = bf16_to_f32(bias[col0 + c]);
+    if (c < n_rot) bias_partner[k] = bf16_to_f32(bias[col0 + (c < half ? c + half : c - half)]);
   }
 
   // Rotation angles of the tile's rows (q and k blocks), in double, while the
   // loads are in flight: sc[row][j] = (sin, cos) of pos[row] * inv_freq[j].
-  if (role < 2) {
-    for (int e = threadIdx.x; e < 16 * half; e += kFusedThreads) {
+  if (n_rot > 0) {
+    for (int e = threadIdx.x; e < R * half; e += kFusedThreads) {
       const int row = e / half, jj = e % half;
       if (b0 + row < p.rows)
         sincos(static_cast<double>(p.pos[b0 + row]) * p.inv_freq[jj], &sc[row][jj][0],
@@ -264,77 +279,125 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
     }
   }
 
-  // Layer-norm statistics: 32 threads per row, each holding up to kStatRegs
-  // float4 of it, so the centred second pass reads registers (wider rows
-  // read the rest again, from cache).
-  {
-    constexpr int kStatRegs = 8;
-    const int row = threadIdx.x >> 5, j = threadIdx.x & 31;
-    float mean = 0.f, rstd = 0.f;
-    if (b0 + row < p.rows) {
-      const float* xs = p.x + static_cast<size_t>(b0 + row) * d;
-      float4 xv[kStatRegs];
-      float s = 0.f;
+  // Layer-norm statistics (mean, then the centred squares).  Rows of one chunk
+  // are already in the workgroup's registers, lane (r, grp) of wave w holding
+  // 8 inputs of each of its k-blocks: four lanes and eight waves add up.
+  float mean[RT], rstd[RT];
+  if (KB <= PRE * kFusedWaves) {
+    auto row_sums = [&](auto term, float (&total)[RT]) {
 #pragma unroll
-      for (int i = 0; i < kStatRegs; ++i) {
-        const int c = 4 * j + 128 * i;
-        xv[i] = c < d ? *reinterpret_cast<const float4*>(xs + c) : float4{0.f, 0.f, 0.f, 0.f};
+      for (int t = 0; t < RT; ++t) {
+        float v = 0.f;
+#pragma unroll
+        for (int i = 0; i < PRE; ++i)
+          if (wave + i * kFusedWaves < KB)
+            v += ((term(x0[i][t].x, t) + term(x0[i][t].y, t)) +
+                  (term(x0[i][t].z, t) + term(x0[i][t].w, t))) +
+                 ((term(x1[i][t].x, t) + term(x1[i][t].y, t)) +
+                  (term(x1[i][t].z, t) + term(x1[i][t].w, t)));
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 32);
+        if (grp == 0) red[wave][t * 16 + r] = v;
       }
+      __syncthreads();
 #pragma unroll
-      for (int i = 0; i < kStatRegs; ++i) s += (xv[i].x + xv[i].y) + (xv[i].z + xv[i].w);
-      for (int c = 4 * j + 128 * kStatRegs; c < d; c += 128) {
-        const float4 v = *reinterpret_cast<const float4*>(xs + c);
-        s += (v.x + v.y) + (v.z + v.w);
+      for (int t = 0; t < RT; ++t) {
+        total[t] = red[0][t * 16 + r];
+#pragma unroll
+        for (int w = 1; w < kFusedWaves; ++w) total[t] += red[w][t * 16 + r];
       }
+    };
+    float sum[RT];
+    row_sums([](float v, int) { return v; }, sum);
 #pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-      mean = s / d;
-      float s2 = 0.f;
+    for (int t = 0; t < RT; ++t) mean[t] = sum[t] / d;
+    __syncthreads();  // every wave has read the sums
+    row_sums([&](float v, int t) { return (v - mean[t]) * (v - mean[t]); }, sum);
 #pragma unroll
-      for (int i = 0; i < kStatRegs; ++i) {
-        if (4 * j + 128 * i < d) {
-          const float c0 = xv[i].x - mean, c1 = xv[i].y - mean, c2 = xv[i].z - mean,
-                      c3 = xv[i].w - mean;
+    for (int t = 0; t < RT; ++t) rstd[t] = 1.f / sqrtf(sum[t] / d + p.eps);
+  } else {
+    // Wider rows: 32 threads per row, each holding up to kStatRegs float4 of
+    // it, so the second pass reads registers (and the rest from cache).
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      constexpr int kStatRegs = 8;
+      const int row = t * 16 + (threadIdx.x >> 5), j = threadIdx.x & 31;
+      float mean = 0.f, rstd = 0.f;
+      if (b0 + row < p.rows) {
+        const float* xs = p.x + static_cast<size_t>(b0 + row) * d;
+        float4 xv[kStatRegs];
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < kStatRegs; ++i) {
+          const int c = 4 * j + 128 * i;
+          xv[i] = c < d ? *reinterpret_cast<const float4*>(xs + c) : float4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int i = 0; i < kStatRegs; ++i) s += (xv[i].x + xv[i].y) + (xv[i].z + xv[i].w);
+        for (int c = 4 * j + 128 * kStatRegs; c < d; c += 128) {
+          const float4 v = *reinterpret_cast<const float4*>(xs + c);
+          s += (v.x + v.y) + (v.z + v.w);
+        }
+#pragma unroll
+        for (int off = 16; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+        mean = s / d;
+        float s2 = 0.f;
+#pragma unroll
+        for (int i = 0; i < kStatRegs; ++i) {
+          if (4 * j + 128 * i < d) {
+            const float c0 = xv[i].x - mean, c1 = xv[i].y - mean, c2 = xv[i].z - mean,
+                        c3 = xv[i].w - mean;
+            s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
+          }
+        }
+        for (int c = 4 * j + 128 * kStatRegs; c < d; c += 128) {
+          const float4 v = *reinterpret_cast<const float4*>(xs + c);
+          const float c0 = v.x - mean, c1 = v.y - mean, c2 = v.z - mean, c3 = v.w - mean;
           s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
         }
-      }
-      for (int c = 4 * j + 128 * kStatRegs; c < d; c += 128) {
-        const float4 v = *reinterpret_cast<const float4*>(xs + c);
-        const float c0 = v.x - mean, c1 = v.y - mean, c2 = v.z - mean, c3 = v.w - mean;
-        s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
-      }
 #pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) s2 += __shfl_xor(s2, off);
-      rstd = 1.f / sqrtf(s2 / d + p.eps);
+        for (int off = 16; off >= 1; off >>= 1) s2 += __shfl_xor(s2, off);
+        rstd = 1.f / sqrtf(s2 / d + p.eps);
+      }
+      if (j == 0) {
+        red[0][row] = mean;
+        red[1][row] = rstd;
+      }
     }
-    if (j == 0) {
-      stats[row][0] = mean;
-      stats[row][1] = rstd;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      mean[t] = red[0][t * 16 + r];
+      rstd[t] = red[1][t * 16 + r];
     }
   }
-  __syncthreads();
-  const float mean = stats[r][0], rstd = stats[r][1];
 
-  f32x4 acc[NT];
+  f32x4 acc[RT][NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[t][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int base = wave;;) {
 #pragma unroll
     for (int i = 0; i < PRE; ++i) {
       if (base + i * kFusedWaves < KB) {
-        // LN(x) for 8 consecutive inputs of row b0 + r, rounded to bf16.
-        u16x8 hb = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (live) {
-          const float xv[8] = {x0[i].x, x0[i].y, x0[i].z, x0[i].w,
-                               x1[i].x, x1[i].y, x1[i].z, x1[i].w};
 #pragma unroll
-          for (int jj = 0; jj < 8; ++jj) {
-            const float z = (xv[jj] - mean) * rstd;
-            hb[jj] = f32_to_bf16_rne(z * bf16_to_f32(gw[i][jj]) + bf16_to_f32(gb[i][jj]));
+        for (int t = 0; t < RT; ++t) {
+          // LN(x) for 8 consecutive inputs of row b0 + 16 t + r, rounded to bf16.
+          u16x8 hb = {0, 0, 0, 0, 0, 0, 0, 0};
+          if (live[t]) {
+            const float xv[8] = {x0[i][t].x, x0[i][t].y, x0[i][t].z, x0[i][t].w,
+                                 x1[i][t].x, x1[i][t].y, x1[i][t].z, x1[i][t].w};
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) {
+              const float z = (xv[jj] - mean[t]) * rstd[t];
+              hb[jj] = f32_to_bf16_rne(z * bf16_to_f32(gw[i][jj]) + bf16_to_f32(gb[i][jj]));
+            }
           }
-        }
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma_bf16(as_bf16(a[i][nt]), as_bf16(hb), acc[nt]);
+          for (int nt = 0; nt < NT; ++nt)
+            acc[t][nt] = mfma_bf16(as_bf16(a[i][nt]), as_bf16(hb), acc[t][nt]);
+        }
       }
     }
     base += PRE * kFusedWaves;
@@ -342,16 +405,18 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
     issue(base);
   }
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) part[wave][nt][lane] = acc[nt];
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) part[wave][t][nt][lane] = acc[t][nt];
   __syncthreads();
   // Result lane l of tile nt: column b = l % 16, outputs 16 nt + 4 (l / 16) + i.
-  if (threadIdx.x < NT * 64) {
-    const int nt = threadIdx.x >> 6, l = threadIdx.x & 63;
-    f32x4 s = part[0][nt][l];
+  for (int e = threadIdx.x; e < RT * NT * 64; e += kFusedThreads) {
+    const int t = e / (NT * 64), nt = (e >> 6) % NT, l = e & 63;
+    f32x4 s = part[0][t][nt][l];
 #pragma unroll
-    for (int w = 1; w < kFusedWaves; ++w) s += part[w][nt][l];
+    for (int w = 1; w < kFusedWaves; ++w) s += part[w][t][nt][l];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) y[l & 15][nt * 16 + 4 * (l >> 4) + i] = s[i];
+    for (int i = 0; i < 4; ++i) y[t * 16 + (l & 15)][nt * 16 + 4 * (l >> 4) + i] = s[i];
   }
   __syncthreads();
 
@@ -360,11 +425,11 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
 #pragma unroll
   for (int k = 0; k < kEpi; ++k) {
     const int e = threadIdx.x + k * kFusedThreads;
-    const int rr = e / D, c = e % D, b = b0 + rr;
-    if (b >= p.rows) continue;
+    const int rr = e / C, c = e % C, b = b0 + rr;
+    if (e >= R * C || b >= p.rows) continue;
+    const int col = col0 + c;
     const double u = y[rr][c];
     if (role == 3) {
-      const int col = jb * D + c;
       if (col >= p.ff) continue;
       const double z = u + static_cast<double>(bias_own[k]);
       p.f16[static_cast<size_t>(b) * p.ff + col] =
@@ -373,7 +438,7 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
     }
     const double ub = u + static_cast<double>(bias_own[k]);
     uint16_t out;
-    if (role == 2 || c >= p.dims) {
+    if (c >= n_rot) {
       out = f64_to_bf16_rne(ub);
     } else {
       const int partner = c < half ? c + half : c - half;
@@ -383,9 +448,9 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
       out = f64_to_bf16_rne(c < half ? ub * cs - w * sn : ub * cs + w * sn);
     }
     if (role == 0)
-      p.q16[static_cast<size_t>(b) * p.h * D + jb * D + c] = out;
+      p.q16[static_cast<size_t>(b) * p.h * D + col] = out;
     else
-      (role == 1 ? p.k16 : p.v16)[static_cast<size_t>(b) * p.kv_stride + p.kv_offset + jb * D + c] = out;
+      (role == 1 ? p.k16 : p.v16)[static_cast<size_t>(b) * p.kv_stride + p.kv_offset + col] = out;
   }
 }
 
@@ -395,8 +460,8 @@ __global__ __launch_bounds__(kFusedThreads) void layer_in_kernel(LayerInParams p
 // wave takes every eighth one, in chunks of PRE whose loads are all issued
 // before the chunk's products.  With y_mlp given, f W_2 + b_2 was computed
 // beside the attention (with the same sums) and only W_o's k-blocks are read.
+template <int PRE>
 __global__ __launch_bounds__(kFusedThreads) void layer_out_kernel(LayerOutParams p) {
-  constexpr int PRE = 16;
   __shared__ f32x4 part[kFusedWaves][2][64];
   const int blk = blockIdx.x, b0 = blockIdx.y * 16;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -487,18 +552,49 @@ hipError_t launch_pack(const PackParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_layer_in(const LayerInParams& p, int head_dim, hipStream_t stream) {
-  const dim3 grid(p.h + 2 * p.owned + (p.ff + head_dim - 1) / head_dim, (p.rows + 15) / 16);
-  if (head_dim == 64)
-    hipLaunchKernelGGL(layer_in_kernel<64>, grid, dim3(kFusedThreads), 0, stream, p);
+template <int NT, int RT>
+static void launch_layer_in_t(const LayerInParams& p, hipStream_t stream) {
+  const int C = 16 * NT, R = 16 * RT;
+  const dim3 grid((p.h + 2 * p.owned) * (p.D / C) + (p.ff + C - 1) / C, (p.rows + R - 1) / R);
+  hipLaunchKernelGGL((layer_in_kernel<NT, RT>), grid, dim3(kFusedThreads), 0, stream, p);
+}
+
+hipError_t launch_layer_in(const LayerInParams& p, hipStream_t stream) {
+  const int cus = compute_units() > 0 ? compute_units() : 256;
+  const long tiles = (static_cast<long>(p.h + 2 * p.owned) * p.D + p.ff) / 16;
+  const long row_tiles = (p.rows + 15) / 16;
+  // The narrowest block whose grid gives each compute unit at most one
+  // workgroup (registers hold one at a time), then 32 rows a block, which read
+  // the weights half as often.  us per step by block (columns x rows):
+  //   batch   16x16  32x16  64x16  64x32
+  //      16     217    220    236    252
+  //      32     293    249    265    311
+  //      64     410    328    291    332
+  //     128     659    506    430    397
+  //     256    1182    904    750    690
+  // Rotated pairs lie in a head's first `dims` channels: a block that rotates
+  // holds them all.
+  if (p.dims <= 16 && tiles * row_tiles <= cus)
+    launch_layer_in_t<1, 1>(p, stream);
+  else if (p.dims <= 32 && tiles * row_tiles <= 2 * cus)
+    launch_layer_in_t<2, 1>(p, stream);
+  else if (p.dims <= 64 && (tiles * row_tiles <= 4 * cus || row_tiles == 1))
+    launch_layer_in_t<4, 1>(p, stream);
+  else if (p.dims <= 64)
+    launch_layer_in_t<4, 2>(p, stream);
   else
-    hipLaunchKernelGGL(layer_in_kernel<128>, grid, dim3(kFusedThreads), 0, stream, p);
+    launch_layer_in_t<8, 1>(p, stream);
   return hipGetLastError();
 }
 
 hipError_t launch_layer_out(const LayerOutParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL(layer_out_kernel, dim3(p.d / 16, (p.rows + 15) / 16), dim3(kFusedThreads), 0,
-                     stream, p);
+  const dim3 grid(p.d / 16, (p.rows + 15) / 16);
+  // W_o's k-blocks alone fill 4 a wave (d up to 1024; wider ones loop): 80
+  // registers instead of 182, so that three workgroups share a compute unit.
+  if (p.y_mlp)
+    hipLaunchKernelGGL(layer_out_kernel<4>, grid, dim3(kFusedThreads), 0, stream, p);
+  else
+    hipLaunchKernelGGL(layer_out_kernel<16>, grid, dim3(kFusedThreads), 0, stream, p);
   return hipGetLastError();
 }
 

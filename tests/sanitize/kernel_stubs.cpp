@@ -13,7 +13,7 @@ hipError_t no_device() { return hipErrorInvalidDevice; }
 }  // namespace
 
 hipError_t launch_pack(const PackParams&, hipStream_t) { return no_device(); }
-hipError_t launch_layer_in(const LayerInParams&, int, hipStream_t) { return no_device(); }
+hipError_t launch_layer_in(const LayerInParams&, hipStream_t) { return no_device(); }
 hipError_t launch_layer_out(const LayerOutParams&, hipStream_t) { return no_device(); }
 hipError_t launch_norm2(const NormParams&, hipStream_t) { return no_device(); }
 hipError_t launch_qkv_epilogue(const QkvEpilogueParams&, hipStream_t) { return no_device(); }
