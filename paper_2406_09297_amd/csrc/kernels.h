@@ -11,6 +11,7 @@ namespace mlkv {
 // step the cosine and sine of each pair's angle at the token's position are
 // tabulated in double, cs[(b*half + j)*2 + {0, 1}]; the attention launches
 // rotate their queries and the owners' appends their keys from that table.
+// (A step of one launch and few workgroups takes them itself: StepParams.)
 // inv_freq[j] = base^(-2j/(2*half)): radians pair j turns by per position.
 constexpr int kMaxRopePairs = 64;
 struct RopeTableParams {
@@ -155,8 +156,9 @@ struct StepParams {
   int* counters;             // [units*chunks] finished runs (zero between calls)
   float* part_acc;           // [units*chunks][runs][chunk_rows][D]  unnormalised partial outputs
   float* part_ml;            // [units*chunks][runs][chunk_rows][2]  (max in log2 units, denominator)
-  const double* rope_cs;     // [B][rope_half][2] cos, sin at the token's position, or null
-  int rope_half;
+  int rope_half;             // rotated channel pairs (0: none)
+  const double* rope_cs;     // [B][rope_half][2] cos, sin at the token's position, or null:
+                             // taken in the kernel from inv_freq
   int B, h, S, n_kv;
   int layers, kv_per_layer, G;
   int chunks, chunk_rows;    // a unit's rows in `chunks` parts of at most chunk_rows
@@ -166,6 +168,7 @@ struct StepParams {
   int max_len;               // attended lengths are clamped to this (<= S)
   int out_bf16;
   float scale_log2;          // log2(e) / sqrt(D)
+  double inv_freq[kMaxRopePairs];
 };
 
 // ---- GPT-NeoX layer pieces around attention (model.hip) ----

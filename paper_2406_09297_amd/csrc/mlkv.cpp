@@ -1011,11 +1011,32 @@ mlkv_status decode_step_check(const void* q_all, const void* k_new_all, const vo
 }
 
 // The step in one launch (step.hip).
+// Workgroups per compute unit from which a step launches a rotary table first:
+// below, its workgroups take the sines themselves under the first tiles' loads
+// and the launch is saved (us with sines taken / with a table: 4.5 workgroups a
+// unit 18.6 / 20.4, 9 30.7 / 32.1, 36 370.4 / 371.7); with many short rounds
+// the sines add up (72, MHA at 128 sequences of 64 .. 128 tokens: 229 / 212).
+constexpr long kStepTableRounds = 48;
+
+// The rotary table of a step, cs [B][half][2].
+mlkv_status rope_table(const int32_t* pos, double* cs, int B, const double* inv_freq, int half,
+                       hipStream_t stream) {
+  mlkv::RopeTableParams p{};
+  p.pos = pos;
+  p.cs = cs;
+  p.B = B;
+  p.half = half;
+  for (int j = 0; j < half; ++j) p.inv_freq[j] = inv_freq[j];
+  const hipError_t err = mlkv::launch_rope_table(p, stream);
+  if (err != hipSuccess) return fail(MLKV_ERR_HIP, "rotary table launch: %s", hipGetErrorString(err));
+  return MLKV_OK;
+}
+
 mlkv_status step_launch(const void* q_all, const uint16_t* k_new, const uint16_t* v_new,
                         const mlkv_cache* cache, const mlkv_map* map, const int32_t* ctx_lens,
                         void* out_all, mlkv_out_dtype out_dtype, int max_len_hint, void* workspace,
-                        size_t workspace_bytes, hipStream_t stream, const double* rope_cs,
-                        int rope_half) {
+                        size_t workspace_bytes, hipStream_t stream, double* rope_cs,
+                        const double* inv_freq, int rope_half) {
   const int B = cache->batch, D = cache->head_dim;
   const int max_len = max_len_of(cache, max_len_hint);
   const StepPlan pl = step_plan(map, B, max_len, D, workspace ? workspace_bytes : 0);
@@ -1033,8 +1054,13 @@ mlkv_status step_launch(const void* q_all, const uint16_t* k_new, const uint16_t
     p.part_acc = reinterpret_cast<float*>(base + kCounterSlots * sizeof(int32_t));
     p.part_ml = reinterpret_cast<float*>(base + pl.ml);
   }
-  p.rope_cs = rope_half > 0 ? rope_cs : nullptr;
-  p.rope_half = rope_half > 0 ? rope_half : 0;
+  p.rope_half = rope_half;
+  for (int j = 0; j < rope_half; ++j) p.inv_freq[j] = inv_freq[j];
+  if (rope_half > 0 && pl.units * pl.chunks > kStepTableRounds * compute_units_or_fallback()) {
+    const mlkv_status s = rope_table(ctx_lens, rope_cs, B, inv_freq, rope_half, stream);
+    if (s != MLKV_OK) return s;
+    p.rope_cs = rope_cs;
+  }
   p.B = B;
   p.h = map->h;
   p.S = cache->capacity;
@@ -1060,14 +1086,15 @@ mlkv_status step_launch(const void* q_all, const uint16_t* k_new, const uint16_t
   return ok();
 }
 
-// The step's launches: one for all layers where the map allows, else per
-// layer the append it owns (when not fused) and its attention.
+// The step's launches: one for all layers where the map allows, else the
+// rotary table (rope_cs [B][rope_half][2]) and per layer the append it owns
+// (when not fused) and its attention.
 mlkv_status decode_step_launch(const void* q_all, const void* k_new_all, const void* v_new_all,
                                const mlkv_cache* cache, const mlkv_map* map,
                                const int32_t* ctx_lens, void* out_all, mlkv_out_dtype out_dtype,
                                int max_len_hint, void* workspace, size_t workspace_bytes,
-                               hipStream_t stream, const double* rope_cs = nullptr,
-                               int rope_half = 0) {
+                               hipStream_t stream, double* rope_cs = nullptr,
+                               const double* inv_freq = nullptr, int rope_half = 0) {
   mlkv_status s;
   const int B = cache->batch, h = map->h, D = cache->head_dim, n_kv = map->n_kv;
   const size_t layer_elems = static_cast<size_t>(B) * h * D;
@@ -1076,7 +1103,10 @@ mlkv_status decode_step_launch(const void* q_all, const void* k_new_all, const v
   const uint16_t* v_new = static_cast<const uint16_t*>(v_new_all);
   if (step_in_one_launch(map, B, D))
     return step_launch(q_all, k_new, v_new, cache, map, ctx_lens, out_all, out_dtype, max_len_hint,
-                       workspace, workspace_bytes, stream, rope_cs, rope_half);
+                       workspace, workspace_bytes, stream, rope_cs, inv_freq, rope_half);
+  if (rope_half > 0 &&
+      (s = rope_table(ctx_lens, rope_cs, B, inv_freq, rope_half, stream)) != MLKV_OK)
+    return s;
   PlanKey planned_key;
   for (int n = 0; n < map->l; ++n) {
     // The attention launch appends the heads the layer owns when it reads
@@ -1175,19 +1205,11 @@ mlkv_status mlkv_decode_step_rope(const void* q_all, const void* k_new_all, cons
                              max_len_hint, ws, ws_bytes, stream)) != MLKV_OK)
     return s;
   const int half = rotary_dims / 2;
-  double* cs = static_cast<double*>(workspace);
-  if (half > 0) {
-    mlkv::RopeTableParams p{};
-    p.pos = ctx_lens;
-    p.cs = cs;
-    p.B = cache->batch;
-    p.half = half;
-    for (int j = 0; j < half; ++j) p.inv_freq[j] = std::pow(rotary_base, -2.0 * j / rotary_dims);
-    const hipError_t err = mlkv::launch_rope_table(p, stream);
-    if (err != hipSuccess) return fail(MLKV_ERR_HIP, "rotary table launch: %s", hipGetErrorString(err));
-  }
+  double inv_freq[mlkv::kMaxRopePairs];
+  for (int j = 0; j < half; ++j) inv_freq[j] = std::pow(rotary_base, -2.0 * j / rotary_dims);
   return decode_step_launch(q_all, k_new_all, v_new_all, cache, map, ctx_lens, out_all, out_dtype,
-                            max_len_hint, ws, ws_bytes, stream, half > 0 ? cs : nullptr, half);
+                            max_len_hint, ws, ws_bytes, stream, static_cast<double*>(workspace),
+                            inv_freq, half);
 }
 
 mlkv_status mlkv_cache_append_rows(int layer, const mlkv_map* map, const mlkv_cache* cache,

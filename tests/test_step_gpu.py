@@ -156,3 +156,27 @@ def test_small_workspace_and_bf16_and_rotation():
     oracle.decode_step_rope(dw.host["q"], k, v, dw.host["k_new"], dw.host["v_new"], dw.kv_of,
                             dw.owner_of, dw.host["ctx"], 16, 10000.0)
     assert np.array_equal(k_gpu, k)
+
+
+@pytest.mark.parametrize("l,h,m,g,D,B,top,rd", [
+    (4, 9, 2, 1, 64, 9, 900, 32),     # two blocks of rows, split runs
+    (6, 12, 2, 1, 64, 130, 95, 64),   # four waves: more row chunks to turn than threads
+    (12, 12, 1, 1, 64, 2, 2047, 16),  # rows in several chunks, most runs per unit
+    (8, 8, 1, 2, 128, 3, 1500, 128),  # head dim 128, every channel turned
+    (12, 12, 12, 12, 64, 86, 30, 16),  # 12384 units: the angles from a table
+])
+def test_rotated_step_matches_oracle(l, h, m, g, D, B, top, rd):
+    tag = f"one launch rotated l{l} h{h} m{m} g{g} D{D} B{B} top{top} rd{rd}"
+    say(tag)
+    dw = _prepare(l, h, m, g, D, B, top, seed=71 + l + h + rd)
+    ws = mlkv.workspace(dw.map, B, dw.S, D, rotary_dims=rd)
+    out = _step(dw, ws=ws, rd=rd)
+    assert np.array_equal(out, _step(dw, ws=ws, rd=rd)), f"{tag}: a repeated step differs"
+    k_gpu, v_gpu = dw.read_cache()
+    k, v = dw.host["k_cache"].copy(), dw.host["v_cache"].copy()
+    ref, q_rot, _ = oracle.decode_step_rope(dw.host["q"], k, v, dw.host["k_new"],
+                                            dw.host["v_new"], dw.kv_of, dw.owner_of,
+                                            dw.host["ctx"], rd, 10000.0, return_rotated=True)
+    assert np.array_equal(k_gpu, k) and np.array_equal(v_gpu, v), f"{tag}: cache differs"
+    check_close(out, ref, tag, bound=step_rounding_bound(q_rot, k, v, dw.kv_of, dw.host["ctx"],
+                                                         ref))
