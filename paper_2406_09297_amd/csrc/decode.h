@@ -54,6 +54,12 @@ __device__ __forceinline__ int partner_chunk(int c0, int half) {
   return c0 < half ? c0 + half : c0 - half;
 }
 
+// What partial results of a row are weighed against: their largest maximum M.
+// Where it is -inf no part has a score above that: against 0 an empty part
+// counts nothing (2^-inf = 0, times sums of 0), and the non-finite sums of a
+// part whose scores were NaN or -inf stay non-finite (0 * NaN).
+__device__ __forceinline__ float merge_reference(float M) { return M == -INFINITY ? 0.f : M; }
+
 // acc / den with one reciprocal (within one ulp) for the four channels; zeros
 // for an empty row (den = 0).  A row with any attended position has den >= 1
 // (its largest weight is at least one), and den = 1 leaves acc exact;

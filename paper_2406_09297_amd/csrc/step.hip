@@ -329,15 +329,14 @@ void step_kernel(StepParams p) {
       mw[w] = sm.m[w][rr];
       M = fmaxf(M, mw[w]);
     }
+    const float ref = merge_reference(M);
     float wsum = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    if (M != -INFINITY) {
 #pragma unroll
-      for (int w = 0; w < W; ++w) {
-        const float f = fast_exp2(mw[w] - M);
-        wsum += f * sm.l[w][rr];
-        o += f * *reinterpret_cast<const f32x4*>(&sm.acc[w][rr][d]);
-      }
+    for (int w = 0; w < W; ++w) {
+      const float f = fast_exp2(mw[w] - ref);
+      wsum += f * sm.l[w][rr];
+      o += f * *reinterpret_cast<const f32x4*>(&sm.acc[w][rr][d]);
     }
     if (!SPLIT || nb == 1) {
       store4_as<D>(p.out, p.out_bf16, row_of(row0 + rr), d, normalize4(o, wsum));
@@ -413,6 +412,12 @@ void step_kernel(StepParams p) {
           o[i] += f * a[u][i];
         }
         M[i] = bm;
+      } else {  // no run so far has a score above -inf: their sums are zeros or NaN
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          den[i] += w[u][i];
+          o[i] += a[u][i];
+        }
       }
     }
   }

@@ -336,6 +336,36 @@ def test_non_finite_inputs_propagate_as_in_the_definition():
                     bound=bound[keep])
 
 
+def test_rows_without_a_score_are_nan_in_every_plan():
+    """A NaN query (no score compares above -inf) and a sequence whose first
+    400 keys are NaN, so that whole runs hold no score: NaN, as the oracle
+    gives, under every plan; the empty sequence stays zero."""
+    lens = np.array([300, 900, 900, 0, 70], np.int32)
+    w = _sweep_workload(64, 4, 1, lens, h=12, l=4, seed=62)
+    dw = DeviceWorkload(w)
+    q, kc, vc = dw.host["q"], dw.host["k_cache"], dw.host["v_cache"]
+    q[0, [0, 3, 4], [2, 1, 11], 7] = synth.BF16_NAN
+    kc[0, 1, :400] = synth.BF16_NAN
+    dw.q = mlkv.bf16_tensor(q, "cuda")
+    dw.cache.load_rows(kc, vc)
+    lens_d = torch.from_numpy(lens).cuda()
+    ref = oracle.decode_attention(0, q[0], kc, vc, dw.kv_of, lens)
+    nan = np.isnan(ref)
+    assert nan[0, 2].all() and nan[4, 11].all() and nan[1].all() and not nan[3].any()
+    for wg, comb, wide in (("", "", ""), ("40", "fused", ""), ("40", "kernel", ""), ("", "", "1"),
+                           ("1", "", "")):
+        with plan_env(wg, comb, wide):
+            say(f"rows without a score workgroups={wg or 'auto'} merge={comb or 'auto'} "
+                f"wide={wide or 'auto'}")
+            out = torch.full((w.B, w.h, w.D), 7.0, dtype=torch.float32, device="cuda")
+            mlkv.decode_attention(0, dw.q[0], dw.cache, dw.map, lens_d, out, ws=dw.ws)
+            torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert np.array_equal(np.isnan(got), nan)
+        assert np.all(got[3] == 0)
+        check_close(got[~nan], ref[~nan], "rows without a score: the others")
+
+
 @pytest.mark.parametrize("pos_kind", ["first", "tile_end", "tile_start", "split_edge", "last"])
 def test_needle_token(pos_kind):
     """A key aligned with q and scaled up takes (almost) all weight: o = v_needle

@@ -180,3 +180,38 @@ def test_rotated_step_matches_oracle(l, h, m, g, D, B, top, rd):
     assert np.array_equal(k_gpu, k) and np.array_equal(v_gpu, v), f"{tag}: cache differs"
     check_close(out, ref, tag, bound=step_rounding_bound(q_rot, k, v, dw.kv_of, dw.host["ctx"],
                                                          ref))
+
+
+@pytest.mark.parametrize("l,h,m,g,D,B,top", [
+    (4, 8, 2, 1, 64, 9, 700),     # split runs
+    (8, 8, 1, 2, 128, 9, 600),    # ... of two chunks, head dim 128
+    (6, 12, 2, 1, 64, 130, 700),  # whole units on four waves
+])
+def test_rows_without_a_score_are_nan_and_empty_rows_zero(l, h, m, g, D, B, top):
+    """A NaN query, a NaN newest key that is the only one attended, and a run
+    of NaN keys make their rows NaN, as the definition does; a row that attends
+    nothing is zero even then, and every other row is untouched."""
+    tag = f"step without a score l{l} h{h} m{m} g{g} D{D} B{B}"
+    say(tag)
+    dw = _prepare(l, h, m, g, D, B, top, seed=97 + h)
+    ctx, last = dw.host["ctx"], m * g - 1
+    assert ctx[0] == -1 and ctx[1] == 0 and ctx[8] == top
+    q, k_new, k_cache = dw.host["q"], dw.host["k_new"], dw.host["k_cache"]
+    q[0, 0, 1, 3] = q[1, 7, 2, 5] = synth.BF16_NAN  # an empty sequence's, one of 65 positions
+    k_new[1, 0, 9] = synth.BF16_NAN                 # the only position of sequence 1
+    k_cache[last, 8, :352] = synth.BF16_NAN         # the first half of sequence 8
+    dw.q, dw.k_new = mlkv.bf16_tensor(q, "cuda"), mlkv.bf16_tensor(k_new, "cuda")
+    dw.cache.load_rows(k_cache, dw.host["v_cache"])
+    out = _step(dw)
+    k, v = k_cache.copy(), dw.host["v_cache"].copy()
+    ref = oracle.decode_step(q, k, v, k_new, dw.host["v_new"], dw.kv_of, dw.owner_of, ctx)
+    rows = np.isnan(ref).any(axis=-1)
+    assert rows[1, 7, 2] and rows[:, 1].any() and rows[:, 8].any() and not rows[:, 0].any()
+    assert np.all(np.isnan(out[rows])), f"{tag}: {np.isfinite(out[rows]).sum()} finite values"
+    assert np.all(out[:, 0] == 0)
+    for arr in (q, k, v):  # the rows left read none of the NaN
+        arr[arr == synth.BF16_NAN] = 0
+    ref[rows] = 0
+    out[rows] = 0
+    bound = step_rounding_bound(q, k, v, dw.kv_of, ctx, ref)
+    check_close(out, ref, tag, bound=bound)
