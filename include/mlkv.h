@@ -353,8 +353,8 @@ mlkv_status mlkv_prefill_attention(int layer, const void* q, const mlkv_cache* c
  *   out_all:   device [l][batch][T][h][head_dim], fp32 or bf16.
  * All 16-byte aligned.  Every check is made before anything is launched.
  * Maps whose layers fall into equal groups (as in mlkv_decode_step) append
- * every head's rows in one launch and run all layers in another; others run
- * layer by layer, in the order above. */
+ * every head's rows in one launch and run all layers in another; others, and
+ * calls too large for one grid, run layer by layer, in the order above. */
 mlkv_status mlkv_prefill_step(const void* q_all, const void* k_new_all, const void* v_new_all,
                               const mlkv_cache* cache, const mlkv_map* map,
                               const int32_t* ctx_lens, int T, void* out_all,

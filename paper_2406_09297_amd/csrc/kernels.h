@@ -66,6 +66,9 @@ constexpr int prefill_wave_blocks(int head_dim) { return head_dim == 64 ? 2 : 1;
 constexpr int prefill_rows_per_workgroup(int head_dim) {
   return 4 * 16 * prefill_wave_blocks(head_dim);
 }
+// Units (sequence, KV head) of a launch: a grid has fewer than 2^32 threads
+// along x, and a unit takes up to 512.
+constexpr long kMaxPrefillUnits = 1L << 23;
 struct PrefillParams {
   const uint16_t* q;         // [B][T][h][D] per layer
   const uint16_t* k;         // key plane   [n_kv][B][S][D]

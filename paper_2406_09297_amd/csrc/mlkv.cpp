@@ -1285,11 +1285,12 @@ mlkv_status mlkv_prefill_step(const void* q_all, const void* k_new_all, const vo
   const uint16_t* k_new = static_cast<const uint16_t*>(k_new_all);
   const uint16_t* v_new = static_cast<const uint16_t*>(v_new_all);
   // Maps with equal groups of layers: every head's rows in one append, every
-  // layer in one launch (where heads and row blocks fit the grids).
+  // layer in one launch (where heads, row blocks and units fit the grids).
   const long per_wg = mlkv::prefill_rows_per_workgroup(D);
   const long all_rows = static_cast<long>(T) * map->layers_per_group * map->group[0];
   if (map->layers_per_group > 0 && n_kv <= kMaxGridY &&
-      (all_rows + per_wg - 1) / per_wg <= kMaxGridY) {
+      (all_rows + per_wg - 1) / per_wg <= kMaxGridY &&
+      static_cast<long>(B) * n_kv < mlkv::kMaxPrefillUnits) {
     if ((s = append_rows_impl(0, n_kv, cache, k_new, v_new, T, n_kv * D, ctx_lens, stream)) !=
             MLKV_OK ||
         (s = prefill_impl(0, q_all, cache, map, ctx_lens, T, out_all, out_dtype, stream, true)) !=

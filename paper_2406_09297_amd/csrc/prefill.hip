@@ -334,7 +334,7 @@ hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t stre
   const long units = static_cast<long>(p.B) * p.n_groups;
   if (units * ((rows + kPrefillSplitRows - 1) / kPrefillSplitRows) <= (head_dim == 64 ? 3 : 2) * cus)
     return launch_prefill_split(p, head_dim, stream, start, stop);
-  if (head_dim == 128 &&
+  if (head_dim == 128 && units < kMaxPrefillUnits &&
       units * ((rows + kPrefillWideRows - 1) / kPrefillWideRows) >= 2 * cus)
     return launch_prefill_wide(p, stream, start, stop);
   const int per_wg = prefill_rows_per_workgroup(head_dim);

@@ -6,6 +6,7 @@
 // when every expectation holds.
 #include <cstdio>
 #include <cstdint>
+#include <utility>
 #include <vector>
 
 #include "mlkv.h"
@@ -132,6 +133,25 @@ static void entry_points() {
   mlkv_map_destroy(mp);
 }
 
+extern long stub_prefills, stub_prefill_threads;
+
+// A prefill takes every layer in one launch only where the device takes the
+// grid (fewer than 2^32 threads); beyond, layer by layer as other maps do.
+static void prefill_grids() {
+  for (const auto& c : {std::pair<int, long>{4, 1}, std::pair<int, long>{40000, 512}}) {
+    mlkv_map* mp = nullptr;
+    EXPECT(mlkv_map_create_uniform(512, 1, 512, 1, &mp) == MLKV_OK);
+    mlkv_cache big{addr(0x100000), addr(0x200000), 512, c.first, 32, 64};
+    stub_prefills = stub_prefill_threads = 0;
+    EXPECT(mlkv_prefill_step(addr(0x300000), addr(0x300000), addr(0x300000), &big, mp,
+                             lens(0x400000), 1, addr(0x500000), MLKV_OUT_F32, nullptr) == MLKV_OK);
+    EXPECT(stub_prefills == c.second);
+    EXPECT(stub_prefill_threads < (1L << 32));
+    stub_prefills = -1;
+    mlkv_map_destroy(mp);
+  }
+}
+
 static void model() {
   mlkv_map* mp = nullptr;
   EXPECT(mlkv_map_create_uniform(2, 4, 1, 1, &mp) == MLKV_OK);
@@ -150,6 +170,7 @@ static void model() {
 int main() {
   maps();
   entry_points();
+  prefill_grids();
   model();
   std::printf("host driver: %d failure(s)\n", g_failures);
   return g_failures == 0 ? 0 : 1;

@@ -3,8 +3,12 @@
 // sizing) can be built by a plain C++ compiler with AddressSanitizer and
 // UndefinedBehaviorSanitizer.  A launch reports an error: the sanitizer
 // driver only exercises paths that stop before any launch, and an
-// unexpected MLKV_ERR_HIP would show that one was reached.
+// unexpected MLKV_ERR_HIP would show that one was reached.  Prefill launches
+// succeed while stub_prefills counts them (not negative): the largest grid
+// of theirs, in threads along x as the device counts them, is kept.
 #include "kernels.h"
+
+long stub_prefills = -1, stub_prefill_threads = 0;
 
 namespace mlkv {
 
@@ -22,9 +26,15 @@ hipError_t launch_residual(const ResidualParams&, hipStream_t) { return no_devic
 hipError_t launch_append(const AppendParams&, int, int, hipStream_t) { return no_device(); }
 hipError_t launch_rope_table(const RopeTableParams&, hipStream_t) { return no_device(); }
 hipError_t launch_cache_rows(const CacheRowsParams&, int, hipStream_t) { return no_device(); }
-hipError_t launch_append_rows(const AppendRowsParams&, int, int, hipStream_t) { return no_device(); }
-hipError_t launch_prefill(const PrefillParams&, int, hipStream_t, hipEvent_t, hipEvent_t) {
-  return no_device();
+hipError_t launch_append_rows(const AppendRowsParams&, int, int, hipStream_t) {
+  return stub_prefills < 0 ? no_device() : hipSuccess;
+}
+hipError_t launch_prefill(const PrefillParams& p, int, hipStream_t, hipEvent_t, hipEvent_t) {
+  if (stub_prefills < 0) return no_device();
+  ++stub_prefills;
+  const long threads = static_cast<long>(p.B) * p.n_groups * 256;
+  stub_prefill_threads = threads > stub_prefill_threads ? threads : stub_prefill_threads;
+  return hipSuccess;
 }
 hipError_t launch_attention_main(const AttnParams&, int, hipStream_t, hipEvent_t, hipEvent_t,
                                  const SideProduct*) {
