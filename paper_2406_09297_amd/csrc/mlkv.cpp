@@ -324,18 +324,23 @@ Plan plan(const mlkv_map* map, int layer, int batch, int max_len, int head_dim) 
 // whose partials are twice as many), in at most kMaxStepRuns runs of a unit
 // (one sequence of 32000 tokens: 16 runs 14.1 us; 32 and 64 runs, merged by
 // one workgroup, were slower).
-// waves: a grid of more than one and at most three workgroups per compute
-// unit is resident at once with four waves and not with eight (128 ragged
-// sequences, 512 units: 42.9 against 45.4 us; 96, 384 units: 34.8 against
-// 35.9); larger grids run in rounds and prefer eight (MHA at 32 sequences,
-// 4608 units: 438 against 444 us; 800 units of 200..4000 tokens 101.5 against
-// 102.8).
+// waves: eight on a grid of at most one workgroup per compute unit, else four:
+// waves without a tile still pass the workgroup's barriers and merge, and
+// fewer workgroups of eight are resident at once (us with four / eight, 11
+// workgroups a unit of 1 .. 48 tokens 24.6 / 38.5, 32 heads of 128 at 186 a
+// unit of 8 .. 13 tokens 531 / 1042, 128 ragged sequences at two 42.9 / 45.4).
+// Four stay ahead while a workgroup re-reads rows for another chunk (MLKV-2 at
+// 16 a unit: 0.57 of the time at 250 tokens, 0.94 at 8000).  With one chunk
+// eight gain on grids of several rounds from about 1000 tokens (one block of
+// rows) or 2000 (two) on: up to 2 % on equal lengths, 1 to 10 % on ragged
+// ones, so they are taken where sequences of kLongTiles tiles are allowed.
 struct StepPlan {
   int chunks, chunk_rows, runs, waves;
   long units;
   size_t ml, need;  // offset of the (max, denominator) pairs, bytes in all; 0 without split runs
 };
 constexpr int kMaxStepRuns = 16;
+constexpr int kLongTiles = 64;
 constexpr int kMaxStepChunksBySplit = 5;  // chunks a unit may be cut into to fill the device
 
 StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, size_t ws_bytes) {
@@ -348,8 +353,10 @@ StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, si
   pl.chunks = finer <= kMaxStepChunksBySplit && pl.units * finer <= cus ? finer : fewest;
   pl.chunk_rows = (rows + pl.chunks - 1) / pl.chunks;
   const long groups = pl.units * pl.chunks;  // workgroups without split runs
-  pl.waves = groups > cus && groups <= 3 * cus ? mlkv::default_waves() : mlkv::wide_waves();
-  const long longest = tiles_of(max_len < 1 ? 1 : max_len) / kMinTiles;
+  const int max_tiles = tiles_of(max_len < 1 ? 1 : max_len);
+  const bool rounds = groups > 3 * cus && pl.chunks == 1 && max_tiles >= kLongTiles;
+  pl.waves = groups <= cus || rounds ? mlkv::wide_waves() : mlkv::default_waves();
+  const long longest = max_tiles / kMinTiles;
   long runs = cus / groups;
   runs = runs < longest ? runs : longest;
   runs = runs < 1 ? 1 : runs > kMaxStepRuns ? kMaxStepRuns : runs;

@@ -21,8 +21,8 @@
 // MLKV-4: 42.4 us against 145 us; eight of 32768 tokens: 54 against 211 us.
 // A third tile in flight per wave spills (184 us) and is no faster where it
 // fits; eight waves on a unit shorten the stream of a lone workgroup but hold
-// only one workgroup per compute unit, so the host gives eight waves to grids
-// of at most one workgroup per compute unit and to grids of several rounds.
+// fewer workgroups per compute unit, so the host gives eight waves to grids of
+// at most one workgroup per compute unit and to several rounds of long sequences.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -71,7 +71,7 @@ def _check(dw, tag):
     (12, 12, 1, 1, 64, 2, 2047),   # 144 rows in five chunks, most runs per unit
     (6, 12, 2, 1, 64, 130, 95),    # 260 units: three blocks on four-wave workgroups
     (12, 12, 1, 1, 64, 60, 95),    # 60 units x 144 rows: three chunks of three blocks
-    (4, 2, 4, 2, 64, 100, 40),     # 800 units: eight waves, whole units
+    (4, 2, 4, 2, 64, 100, 40),     # 800 units of at most two tiles: four waves, whole units
     (4, 8, 2, 2, 128, 9, 500),     # head dim 128, eight rows
     (8, 8, 1, 2, 128, 3, 1500),    # 32 rows in two chunks, split runs
     (8, 8, 1, 2, 128, 150, 40),    # 300 units: two blocks on four-wave workgroups
@@ -215,3 +215,31 @@ def test_rows_without_a_score_are_nan_and_empty_rows_zero(l, h, m, g, D, B, top)
     out[rows] = 0
     bound = step_rounding_bound(q, k, v, dw.kv_of, ctx, ref)
     check_close(out, ref, tag, bound=bound)
+
+
+@pytest.mark.parametrize("l,h,m,g,D,B", [
+    (2, 2, 2, 2, 64, 193),   # 772 units: one block of rows
+    (4, 32, 1, 4, 64, 193),  # ... two blocks
+    (2, 2, 2, 2, 128, 193),
+    (4, 32, 1, 4, 128, 193),
+])
+def test_eight_waves_on_whole_units(l, h, m, g, D, B):
+    """Several rounds of workgroups over sequences allowed 64 tiles: eight
+    waves a unit, here with lengths from none to a few tiles and three long."""
+    tag = f"eight waves l{l} h{h} m{m} g{g} D{D}"
+    say(tag)
+    dw = _prepare(l, h, m, g, D, B, 60, seed=41 + D)
+    long = synth.step_inputs(synth.Workload("long", l=l, h=h, m=m, g=g, D=D, B=3, ctx=2047, seed=43))
+    ctx = _lengths(B, 60)
+    ctx[[20, 21, 22]] = (2047, 1024, 900)
+    for name in ("k_cache", "v_cache"):
+        wide = np.full((m * g, B, 2048, D), synth.BF16_NAN, np.uint16)
+        wide[:, :, :60] = dw.host[name][:, :, :60]
+        for i, b in enumerate((20, 21, 22)):
+            wide[:, b, :ctx[b]] = long[name][:, i, :ctx[b]]
+        dw.host[name] = wide
+    dw.host["ctx"], dw.ctx, dw.S = ctx, torch.from_numpy(ctx).cuda(), 2048
+    dw.cache = mlkv.Cache.empty(m * g, B, 2048, D)
+    dw.cache.load_rows(dw.host["k_cache"], dw.host["v_cache"])
+    dw.ws = mlkv.workspace(dw.map, B, 2048, D)
+    _check(dw, tag)
