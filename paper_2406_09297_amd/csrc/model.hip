@@ -572,15 +572,23 @@ hipError_t launch_layer_in(const LayerInParams& p, hipStream_t stream) {
   //      64     410    328    291    332
   //     128     659    506    430    397
   //     256    1182    904    750    690
+  // Heads of 128 channels keep whole-head blocks beyond four 16-column tiles a
+  // compute unit: every column block normalises its rows again, half as often
+  // with 128 columns (us per 4-layer step, 64x32 / 128x16: d 1536, batch 47
+  // 220 / 204; d 2048, batch 70 420 / 373; d 4096, batch 5 413 / 343).
+  // A third tile of at most eight rows leaves half of the 64x32 blocks mostly idle:
+  // there 64x16 up to five tiles a compute unit (d 1536, batch 33 208 / 194 us,
+  // 48 257 / 268).
   // Rotated pairs lie in a head's first `dims` channels: a block that rotates
   // holds them all.
+  const bool thin = row_tiles == 3 && p.rows <= 40 && tiles * row_tiles <= 5 * cus;
   if (p.dims <= 16 && tiles * row_tiles <= cus)
     launch_layer_in_t<1, 1>(p, stream);
   else if (p.dims <= 32 && tiles * row_tiles <= 2 * cus)
     launch_layer_in_t<2, 1>(p, stream);
-  else if (p.dims <= 64 && (tiles * row_tiles <= 4 * cus || row_tiles == 1))
+  else if (p.dims <= 64 && (tiles * row_tiles <= 4 * cus || (p.D == 64 && (row_tiles == 1 || thin))))
     launch_layer_in_t<4, 1>(p, stream);
-  else if (p.dims <= 64)
+  else if (p.D == 64)
     launch_layer_in_t<4, 2>(p, stream);
   else
     launch_layer_in_t<8, 1>(p, stream);
@@ -591,6 +599,9 @@ hipError_t launch_layer_out(const LayerOutParams& p, hipStream_t stream) {
   const dim3 grid(p.d / 16, (p.rows + 15) / 16);
   // W_o's k-blocks alone fill 4 a wave (d up to 1024; wider ones loop): 80
   // registers instead of 182, so that three workgroups share a compute unit.
+  // Steps with 16 instead of 4 take 1.01 .. 1.11 of the time up to d 1536,
+  // 1.00 .. 1.04 at 2048, and 0.99 at one batch tile of 3072 or 4096, where a
+  // wave's two or three chunks are a longer chain than one.
   if (p.y_mlp)
     hipLaunchKernelGGL(layer_out_kernel<4>, grid, dim3(kFusedThreads), 0, stream, p);
   else

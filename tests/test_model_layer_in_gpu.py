@@ -22,8 +22,10 @@ pytestmark = pytest.mark.gpu
     (4, 64, 96, 5, 64),       # 64 columns for the rotation; fc1 ends inside a block
     (4, 64, 1024, 193, 64),   # 64 columns x 32 rows, last row block of one row
     (13, 64, 2080, 100, 64),  # ... rows wider than a chunk
+    (16, 64, 4800, 35, 16),   # 64 columns x 16 rows: a third row block of three rows
     (4, 128, 160, 17, 16),    # head dim 128: eight blocks a head
     (4, 128, 96, 17, 128),    # 128 columns; fc1 ends inside a block
+    (4, 128, 800, 193, 16),   # 128 columns by grid size; one row in the last block
 ])
 def test_layer_in_blocks_match_oracle(h, D, d_ff, B, rd):
     ctx = np.array([(i * 13) % 70 for i in range(B)], np.int32)
