@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime_api.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace mlkv {
@@ -148,6 +149,11 @@ struct AttnSideParams : AttnParams {
 // layer.  Unit u is (sequence u / n_kv, KV head u % n_kv); its rows, layer by
 // layer and head by head, number layers * G.
 constexpr int step_max_blocks(int head_dim) { return head_dim == 64 ? 3 : 2; }  // of 16 rows
+// Most runs of a unit of `tiles` tiles.
+inline __host__ __device__ int step_run_bound(int tiles) {
+  const int root = static_cast<int>(sqrtf(static_cast<float>(tiles)));
+  return root > 16 ? root : 16;
+}
 struct StepParams {
   const uint16_t* q;         // [l][B][h][D]
   const uint16_t* k;         // key plane   [n_kv][B][S][D]
@@ -165,7 +171,7 @@ struct StepParams {
   int B, h, S, n_kv;
   int layers, kv_per_layer, G;
   int chunks, chunk_rows;    // a unit's rows in `chunks` parts of at most chunk_rows
-  int runs, min_tiles;       // most runs of a unit; least tiles of a run when there are several
+  int runs, min_tiles;       // most runs of a unit (beside step_run_bound); least tiles of a run when there are several
   int waves;                 // waves per workgroup: default_waves() or wide_waves()
   unsigned items;            // units * runs
   int max_len;               // attended lengths are clamped to this (<= S)

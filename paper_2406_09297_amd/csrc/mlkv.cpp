@@ -321,9 +321,16 @@ Plan plan(const mlkv_map* map, int layer, int batch, int max_len, int head_dim) 
 // chunks of three blocks, 32 in chunks of two).
 // runs: split only to give every compute unit one workgroup of eight waves
 // (8 x 32768 tokens: 54 us on 256 such workgroups, 64 on 512 of four waves,
-// whose partials are twice as many), in at most kMaxStepRuns runs of a unit
-// (one sequence of 32000 tokens: 16 runs 14.1 us; 32 and 64 runs, merged by
-// one workgroup, were slower).
+// whose partials are twice as many; a few workgroups more, one sequence of
+// 500000 tokens in 3 x 4 chunks, 420 us on 264 and 280 on 192), in at most
+// step_run_bound runs of a unit, the number of its tiles' square root: more
+// runs shorten the stream and lengthen the merge, by one workgroup, as much
+// (us in 16 / 32 / 64 / 128 runs, one head of 64 channels and 8 rows, 32000
+// tokens 13.0 / 11.8 / 13.2 / 18.8, 131000 28.5 / 19.8 / 17.4 / 20.7, 500000
+// 87.5 / 49.7 / 33.3 / 33.7).  Beyond 16 runs, runs for more than half of the
+// compute units are to read kFullRun channels each (16 / 32 runs of eight heads
+// of 64 channels, 131000 tokens 42.3 / 44.6, 500000 189.8 / 175.3; 32 / 64 of
+// four of 128, 131000 45.8 / 48.2, 500000 189.8 / 177.9).
 // waves: eight on a grid of at most one workgroup per compute unit, else four:
 // waves without a tile still pass the workgroup's barriers and merge, and
 // fewer workgroups of eight are resident at once (us with four / eight, 11
@@ -339,8 +346,8 @@ struct StepPlan {
   long units;
   size_t ml, need;  // offset of the (max, denominator) pairs, bytes in all; 0 without split runs
 };
-constexpr int kMaxStepRuns = 16;
 constexpr int kLongTiles = 64;
+constexpr int kFullRun = 3 << 17;
 constexpr int kMaxStepChunksBySplit = 5;  // chunks a unit may be cut into to fill the device
 
 StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, size_t ws_bytes) {
@@ -357,9 +364,15 @@ StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, si
   const bool rounds = groups > 3 * cus && pl.chunks == 1 && max_tiles >= kLongTiles;
   pl.waves = groups <= cus || rounds ? mlkv::wide_waves() : mlkv::default_waves();
   const long longest = max_tiles / kMinTiles;
+  const long bound = mlkv::step_run_bound(max_tiles);
   long runs = cus / groups;
   runs = runs < longest ? runs : longest;
-  runs = runs < 1 ? 1 : runs > kMaxStepRuns ? kMaxStepRuns : runs;
+  runs = runs < 1 ? 1 : runs > bound ? bound : runs;
+  const long half = cus / 2 / pl.units > 16 ? cus / 2 / pl.units : 16;
+  if (runs > half && static_cast<long>(max_tiles) * kTileTokens / runs * head_dim < kFullRun)
+    runs = half;
+  // The grid takes whole rows of eight items (one an XCD) for each chunk.
+  while (runs > 1 && (pl.units * runs + 7) / 8 * 8 * pl.chunks > cus) --runs;
   for (;; --runs) {  // as many as the workspace holds
     pl.runs = static_cast<int>(runs);
     pl.ml = pl.need = 0;
@@ -373,9 +386,17 @@ StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, si
 
 // Whether a step runs in one launch: the map's layers in equal groups, no
 // override of the per-layer plan, and a grid the device takes (2^32 threads;
-// such a step, of more than 4 million units, runs layer by layer).
-bool step_in_one_launch(const mlkv_map* map, int batch, int head_dim) {
+// such a step, of more than 4 million units, runs layer by layer).  The one
+// layer of a map without others shares no reads, and its own kernel merges a
+// unit's runs in several workgroups, which is faster for up to three very long
+// units (us, here / one launch: one of 131000 tokens 13.3 / 17.4, two of 32000
+// with 128 channels 13.3 / 15.8; but one of 32000 with 64 12.3 / 11.8, four of
+// 131000 27.8 / 25.9).
+bool step_in_one_launch(const mlkv_map* map, int batch, int max_len, int head_dim) {
   if (map->layers_per_group <= 0) return false;
+  if (map->l == 1 && static_cast<long>(batch) * map->n_kv <= 3 &&
+      static_cast<long>(max_len) * head_dim > (3L << 20))
+    return false;
   for (const char* name : {"MLKV_WORKGROUPS", "MLKV_COMBINE", "MLKV_WIDE"})
     if (std::getenv(name)) return false;
   const long rows = static_cast<long>(map->layers_per_group) * map->group[0];
@@ -1108,7 +1129,7 @@ mlkv_status decode_step_launch(const void* q_all, const void* k_new_all, const v
   const size_t out_elem_bytes = out_dtype == MLKV_OUT_BF16 ? 2 : 4;
   const uint16_t* k_new = static_cast<const uint16_t*>(k_new_all);
   const uint16_t* v_new = static_cast<const uint16_t*>(v_new_all);
-  if (step_in_one_launch(map, B, D))
+  if (step_in_one_launch(map, B, max_len_of(cache, max_len_hint), D))
     return step_launch(q_all, k_new, v_new, cache, map, ctx_lens, out_all, out_dtype, max_len_hint,
                        workspace, workspace_bytes, stream, rope_cs, inv_freq, rope_half);
   if (rope_half > 0 &&

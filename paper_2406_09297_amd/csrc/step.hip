@@ -152,12 +152,14 @@ void step_kernel(StepParams p) {
   int L = ctx < 0 ? 0 : ctx == INT32_MAX ? ctx : ctx + 1;
   L = L > p.max_len ? p.max_len : L;
   const int tiles = (L + kTile - 1) / kTile;
-  // Runs of this unit: at most p.runs, none shorter than p.min_tiles unless
-  // it is the only one.
+  // Runs of this unit: at most p.runs, which bounds those of the longest, and
+  // what its own tiles allow; none shorter than p.min_tiles unless it is the
+  // only one.
   int nb = 1;
   if constexpr (SPLIT) {
     nb = tiles / p.min_tiles;
     nb = nb < 1 ? 1 : nb > p.runs ? p.runs : nb;
+    nb = min(nb, step_run_bound(tiles));
     if (j >= nb) return;
   }
   const int k0 = static_cast<int>(static_cast<long>(tiles) * j / nb);

@@ -9,6 +9,7 @@
 #include <utility>
 #include <vector>
 
+#include "kernels.h"
 #include "mlkv.h"
 
 static int g_failures = 0;
@@ -152,6 +153,54 @@ static void prefill_grids() {
   }
 }
 
+extern long stub_steps;
+extern mlkv::StepParams stub_step;
+
+// Few long sequences: a unit's runs grow with the square root of its tiles
+// (16 at least), leave a grid of at most one workgroup per compute unit, and
+// fit any workspace that is handed in; a map of one layer on up to three very
+// long units keeps the layer's own kernel.
+static void step_runs() {
+  const struct { int l, h, m, g, D, B, len, runs; } cases[] = {
+      {2, 8, 1, 1, 64, 1, 131072, 64},  {2, 8, 1, 1, 64, 1, 8192, 16},
+      {2, 8, 1, 1, 64, 1, 500000, 125}, {2, 8, 1, 1, 64, 8, 131072, 16},
+      {2, 8, 1, 1, 64, 8, 500000, 32},  {12, 12, 4, 1, 128, 1, 500000, 20},
+      {12, 12, 1, 1, 64, 2, 2048, 8},   {1, 8, 1, 1, 64, 1, 131072, 0},
+      {1, 8, 1, 1, 128, 3, 32768, 0},   {1, 8, 1, 1, 64, 1, 32768, 32},
+      {1, 8, 1, 1, 64, 4, 131072, 32},
+  };
+  for (const auto& c : cases) {
+    mlkv_map* mp = nullptr;
+    EXPECT(mlkv_map_create_uniform(c.l, c.h, c.m, c.g, &mp) == MLKV_OK);
+    mlkv_cache cache{addr(0x100000), addr(0x200000), c.m * c.g, c.B, c.len, c.D};
+    const size_t full = mlkv_workspace_bytes(mp, c.B, c.len, c.D);
+    int last = c.runs;
+    for (size_t ws = full; ws > 0; ws = ws * 4 / 5) {
+      stub_steps = 0;
+      const mlkv_status s = mlkv_decode_step(addr(0x300000), addr(0x300000), addr(0x300000),
+                                             &cache, mp, lens(0x400000), addr(0x500000),
+                                             MLKV_OUT_F32, 0, addr(0x600000), ws, nullptr);
+      const long steps = stub_steps;
+      stub_steps = -1;
+      if (s == MLKV_ERR_WORKSPACE && ws < full) break;
+      EXPECT(s == MLKV_OK && steps == (c.runs > 0 ? 1 : 0));
+      if (steps != 1) continue;
+      const mlkv::StepParams& p = stub_step;
+      if (ws == full) EXPECT(p.runs == c.runs);
+      EXPECT(p.runs >= 1 && p.runs <= last);
+      last = p.runs;
+      if (p.runs == 1) continue;
+      EXPECT((p.items + 7) / 8 * 8 * p.chunks <= 256);
+      const size_t rows = size_t(c.B) * c.m * c.g * p.chunks * p.runs * p.chunk_rows;
+      const char* base = static_cast<char*>(addr(0x600000));
+      EXPECT(reinterpret_cast<char*>(p.part_acc + rows * c.D) <=
+             reinterpret_cast<char*>(p.part_ml));
+      EXPECT(reinterpret_cast<char*>(p.part_ml + rows * 2) <= base + ws);
+    }
+    mlkv_map_destroy(mp);
+  }
+}
+
 static void model() {
   mlkv_map* mp = nullptr;
   EXPECT(mlkv_map_create_uniform(2, 4, 1, 1, &mp) == MLKV_OK);
@@ -171,6 +220,7 @@ int main() {
   maps();
   entry_points();
   prefill_grids();
+  step_runs();
   model();
   std::printf("host driver: %d failure(s)\n", g_failures);
   return g_failures == 0 ? 0 : 1;

@@ -6,9 +6,13 @@
 // unexpected MLKV_ERR_HIP would show that one was reached.  Prefill launches
 // succeed while stub_prefills counts them (not negative): the largest grid
 // of theirs, in threads along x as the device counts them, is kept.
+// Launches of decode steps succeed while stub_steps counts
+// them: the last one of a whole step is kept.
 #include "kernels.h"
 
 long stub_prefills = -1, stub_prefill_threads = 0;
+long stub_steps = -1;
+mlkv::StepParams stub_step;
 
 namespace mlkv {
 
@@ -38,13 +42,16 @@ hipError_t launch_prefill(const PrefillParams& p, int, hipStream_t, hipEvent_t, 
 }
 hipError_t launch_attention_main(const AttnParams&, int, hipStream_t, hipEvent_t, hipEvent_t,
                                  const SideProduct*) {
-  return no_device();
+  return stub_steps < 0 ? no_device() : hipSuccess;
 }
 hipError_t launch_attention_merge(const AttnParams&, int, hipStream_t, hipEvent_t) {
-  return no_device();
+  return stub_steps < 0 ? no_device() : hipSuccess;
 }
-hipError_t launch_step(const StepParams&, int, hipStream_t, hipEvent_t, hipEvent_t) {
-  return no_device();
+hipError_t launch_step(const StepParams& p, int, hipStream_t, hipEvent_t, hipEvent_t) {
+  if (stub_steps < 0) return no_device();
+  ++stub_steps;
+  stub_step = p;
+  return hipSuccess;
 }
 hipError_t launch_fill(uint32_t*, size_t, uint32_t, hipStream_t) { return no_device(); }
 hipError_t launch_empty_timed(int, int, hipStream_t, hipEvent_t, hipEvent_t) { return no_device(); }

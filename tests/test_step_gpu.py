@@ -68,7 +68,7 @@ def _check(dw, tag):
     (4, 8, 2, 1, 64, 9, 700),      # sixteen rows: one full block; split runs
     (4, 9, 2, 1, 64, 9, 900),      # eighteen rows: two blocks, the second nearly empty
     (6, 12, 2, 1, 64, 9, 1300),    # thirty-six rows in two chunks, split runs
-    (12, 12, 1, 1, 64, 2, 2047),   # 144 rows in five chunks, most runs per unit
+    (12, 12, 1, 1, 64, 2, 2047),   # 144 rows in five chunks, eight runs per unit
     (6, 12, 2, 1, 64, 130, 95),    # 260 units: three blocks on four-wave workgroups
     (12, 12, 1, 1, 64, 60, 95),    # 60 units x 144 rows: three chunks of three blocks
     (4, 2, 4, 2, 64, 100, 40),     # 800 units of at most two tiles: four waves, whole units
@@ -81,6 +81,40 @@ def test_one_launch_step_matches_oracle(l, h, m, g, D, B, top):
     tag = f"one launch l{l} h{h} m{m} g{g} D{D} B{B} top{top}"
     say(tag)
     _check(_prepare(l, h, m, g, D, B, top, seed=31 + l + h), tag)
+
+
+@pytest.mark.parametrize("l,h,m,g,D,ctx", [
+    (32, 32, 2, 2, 128, [1500, 700]),       # 256 rows: eight chunks of two blocks, four runs
+    (12, 16, 1, 1, 64, [4200, 1031]),       # 192 rows: four chunks of three blocks, 16 runs
+    (8, 12, 1, 1, 128, [4200]),             # 96 rows, 16 runs merged in two rounds
+    (2, 8, 1, 1, 64, [33000, 9300, 500]),   # 32 runs, 17 by the second one's length
+    (4, 6, 2, 1, 128, [12500]),             # 19 runs of two units
+    (2, 4, 2, 2, 128, [33000, 16000]),      # eight units: 16 runs, half of the compute units
+])
+def test_split_runs_match_oracle(l, h, m, g, D, ctx):
+    """Units in several runs at the widest row blocks, in more runs than a
+    merge takes at a time, and in fewer than the longest unit's."""
+    tag = f"split runs l{l} h{h} m{m} g{g} D{D} ctx{ctx}"
+    say(tag)
+    dw = _prepare(l, h, m, g, D, len(ctx), max(ctx), seed=53 + l + h)
+    dw.host["ctx"] = np.array(ctx, np.int32)
+    dw.ctx = torch.from_numpy(dw.host["ctx"]).cuda()
+    _check(dw, tag)
+
+
+@pytest.mark.parametrize("runs", [1, 2, 3, 7])
+def test_workspace_for_fewer_runs(runs):
+    """A workspace that ends where `runs` runs of each unit end."""
+    dw = _prepare(12, 12, 4, 1, 64, 2, 2000, seed=5)
+    dw.host["ctx"] = np.array([2000, 1100], np.int32)
+    dw.ctx = torch.from_numpy(dw.host["ctx"]).cuda()
+    rows = 2 * 4 * 2 * runs * 18  # sequences x KV heads x chunks x runs x rows of a chunk
+    size = 65536 * 4 + -(-rows * 64 * 4 // 256) * 256 + rows * 8
+    tag = f"workspace for {runs} runs"
+    say(tag)
+    tight = 65536 * 4 + 60 * 1024  # the layer-by-layer step's needs: at least these
+    dw.ws = torch.zeros(max(size, tight), dtype=torch.uint8, device="cuda")
+    _check(dw, tag)
 
 
 @pytest.mark.parametrize("kv_of,owner_of", [
@@ -161,7 +195,7 @@ def test_small_workspace_and_bf16_and_rotation():
 @pytest.mark.parametrize("l,h,m,g,D,B,top,rd", [
     (4, 9, 2, 1, 64, 9, 900, 32),     # two blocks of rows, split runs
     (6, 12, 2, 1, 64, 130, 95, 64),   # four waves: more row chunks to turn than threads
-    (12, 12, 1, 1, 64, 2, 2047, 16),  # rows in several chunks, most runs per unit
+    (12, 12, 1, 1, 64, 2, 2047, 16),  # rows in several chunks, eight runs per unit
     (8, 8, 1, 2, 128, 3, 1500, 128),  # head dim 128, every channel turned
     (12, 12, 12, 12, 64, 86, 30, 16),  # 12384 units: the angles from a table
 ])
