@@ -266,6 +266,53 @@ hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t stre
 // Forms of prefill32.hip, called by launch_prefill where they are faster.
 constexpr int kPrefillWideRows = 256;  // query rows of a workgroup (head dim 128 only)
 constexpr int kPrefillSplitRows = 32;
+
+// The form of a call, by the workgroups each would launch and the cache's
+// capacity, which bounds the positions attended (the host knows no more of
+// them; they are what decides, as under each rule).  us, form taken / plain form.
+enum class PrefillForm { kPlain, kSplit, kWide };
+inline PrefillForm prefill_form(const PrefillParams& p, int head_dim, long cus) {
+  const long rows = static_cast<long>(p.T) * p.layers * p.G;
+  const long units = static_cast<long>(p.B) * p.n_groups;
+  auto blocks = [&](long per_wg) { return units * ((rows + per_wg - 1) / per_wg); };
+  const long split = blocks(kPrefillSplitRows), plain = blocks(prefill_rows_per_workgroup(head_dim));
+  // Split over the tokens where the plain form leaves compute units idle: it
+  // shortens their streams, but every 32 rows read the context again and its
+  // waves are merged, so the more blocks, the longer the contexts it needs.
+  //   64: one block a unit 53 / 131 at 6000 positions, 12 / 12 at none
+  //       two a unit       24 / 37 at 2000, 14 / 16 at 400
+  //       three a unit     26 / 31 at 1600, 26 / 26 at 1000, 15 / 12 at none
+  //   128: one a unit      48 / 100 at 6000, 12 / 11 at none
+  //       two a unit       37 / 41 at 2000, 23 / 23 at 800, 16 / 12 at 200
+  // Plain blocks of few rows, one or two a unit: 133 / 177 at 8000 (64, 1.1 a
+  // unit), 28 / 27 at 1500; above two 209 / 192.  128: 249 / 215.
+  if (head_dim == 64) {
+    if (split <= cus) return PrefillForm::kSplit;
+    if (plain < cus && split <= 2 * cus && p.S >= 512) return PrefillForm::kSplit;
+    if (plain < cus && split <= 3 * cus && p.S >= 1024) return PrefillForm::kSplit;
+    return 4 * split <= 7 * cus && p.S >= 2048 ? PrefillForm::kSplit : PrefillForm::kPlain;
+  }
+  if (plain < cus && split <= cus && p.S >= 256) return PrefillForm::kSplit;
+  if (plain <= cus && (plain < cus || split == 2 * plain) && split <= 2 * cus && p.S >= 1024)
+    return PrefillForm::kSplit;
+  // Wide blocks read the rows a third or a quarter as often.  They pay from two
+  // a unit on for long contexts (93 / 101, 2 x 2048 tokens of 32 heads) and for
+  // more rows than the caches near the units hold (233 / 295, 157 MiB on 400
+  // positions); of several rounds for a quarter of it (259 / 328, 69 MiB), and
+  // of units not a multiple of eight, whose blocks go to other XCDs, for less
+  // (144 / 188, 43 MiB).  Short ones keep the plain form (44 / 34, 128 units of
+  // 1200 rows on none), and mostly empty blocks (37 / 16, units of one row).
+  // Half as often pays on several rounds (182 / 285, 768 units of 100 rows).
+  const long wide = blocks(kPrefillWideRows), mib = units * p.S * 512 >> 20;
+  const bool quarter = wide >= 2 * cus && plain >= 3 * wide &&
+                       (p.S >= 1024 || (mib >= 80 && p.S >= 128) ||
+                        (units % 8 != 0 && mib >= 20) ||
+                        (wide >= 4 * cus && mib >= 40 && p.S >= 384));
+  if (units < kMaxPrefillUnits &&
+      (quarter || (wide >= 3 * cus && plain >= 2 * wide && mib >= 192)))
+    return PrefillForm::kWide;
+  return PrefillForm::kPlain;
+}
 hipError_t launch_prefill_wide(const PrefillParams& p, hipStream_t stream, hipEvent_t start,
                                hipEvent_t stop);
 hipError_t launch_prefill_split(const PrefillParams& p, int head_dim, hipStream_t stream,

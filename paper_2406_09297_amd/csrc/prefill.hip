@@ -322,21 +322,9 @@ __global__ __launch_bounds__(256) void append_rows_kernel(AppendRowsParams p) {
 
 hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t stream,
                           hipEvent_t start, hipEvent_t stop) {
-  // By the workgroups a form launches.  Split over the tokens while 32-row
-  // blocks are at most three (head dim 64) or two (128) per compute unit: with
-  // more, its reads of the whole context by every block cost more than the
-  // idle units of the other form (64: 750 blocks of a 2000-token prompt 23 us
-  // against 36, 1500 blocks 41 against 37; 128: 400 blocks of 400 tokens on
-  // 8000 97 against 131, 800 blocks 194 against 157).  Wide blocks for head
-  // dim 128 from two per compute unit on (prefill32.hip).
-  const long cus = compute_units() > 0 ? compute_units() : 256;
-  const long rows = static_cast<long>(p.T) * p.layers * p.G;
-  const long units = static_cast<long>(p.B) * p.n_groups;
-  if (units * ((rows + kPrefillSplitRows - 1) / kPrefillSplitRows) <= (head_dim == 64 ? 3 : 2) * cus)
-    return launch_prefill_split(p, head_dim, stream, start, stop);
-  if (head_dim == 128 && units < kMaxPrefillUnits &&
-      units * ((rows + kPrefillWideRows - 1) / kPrefillWideRows) >= 2 * cus)
-    return launch_prefill_wide(p, stream, start, stop);
+  const PrefillForm form = prefill_form(p, head_dim, compute_units() > 0 ? compute_units() : 256);
+  if (form == PrefillForm::kSplit) return launch_prefill_split(p, head_dim, stream, start, stop);
+  if (form == PrefillForm::kWide) return launch_prefill_wide(p, stream, start, stop);
   const int per_wg = prefill_rows_per_workgroup(head_dim);
   const int blocks = (p.T * p.layers * p.G + per_wg - 1) / per_wg;
   const dim3 grid(p.B * p.n_groups, blocks);

@@ -221,9 +221,8 @@ __device__ __forceinline__ void prefill_step_tile(PrefillState<D>& st, const uin
 // 256 rows a workgroup, so that a staged byte serves twice the rows it does in
 // prefill.hip's 16-row form, where head dim 128 is bound by LDS reads.  One
 // layer of 32 heads, 2 x 2048 tokens: 92 us in a call with its append against
-// 99; one prompt of 4096: 154 against 171.  Grids of under two workgroups per
-// compute unit are slower than the 64-row workgroups of prefill.hip (2000
-// tokens, 252 workgroups: 65 against 51 us), and head dim 64 gains nothing
+// 99; one prompt of 4096: 154 against 171.  Where it is slower than the 64-row
+// workgroups of prefill.hip stands at prefill_form; head dim 64 gains nothing
 // (744 against 708 us per 12-layer prompt).
 template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -327,7 +326,7 @@ void prefill_wide_kernel(PrefillParams p) {
 
 // ---------------------------------------------------------------------------
 // For calls whose row blocks leave the device idle (few new tokens, long
-// contexts): a workgroup of kSplitWaves waves takes 32 rows, wave w the tiles
+// contexts; prefill_form): a workgroup of kSplitWaves waves takes 32 rows, wave w the tiles
 // w, w + kSplitWaves, ..., straight from the planes to registers, and the
 // waves' partial results are merged through LDS in wave order.  Bound by what a
 // compute unit's load path delivers, about 100 GB/s, as every workgroup reads

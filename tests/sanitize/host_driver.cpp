@@ -153,6 +153,33 @@ static void prefill_grids() {
   }
 }
 
+extern int stub_prefill_form;
+
+// The form of a prefill (0 plain, 1 split over the tokens, 2 wide blocks) at
+// the sizes at which the GPU tests check the forms' results, and where a form
+// was chosen that was slower than the plain one: few tokens on short contexts.
+static void prefill_forms() {
+  const struct { int l, h, m, g, D, B, T, S, form; } cases[] = {
+      {4, 8, 2, 4, 64, 24, 50, 160, 0},   {4, 8, 2, 4, 128, 24, 50, 160, 0},
+      {6, 12, 3, 4, 128, 43, 33, 320, 2}, {2, 12, 2, 1, 64, 2, 80, 544, 1},
+      {2, 12, 2, 1, 128, 2, 80, 544, 1},
+      {1, 32, 1, 32, 128, 101, 1, 64, 0},  {1, 12, 1, 12, 128, 80, 1, 64, 0},
+      {12, 12, 12, 12, 128, 126, 2, 64, 0}, {1, 32, 1, 32, 128, 41, 26, 64, 0},
+      {1, 32, 1, 8, 64, 5, 129, 256, 0},   {1, 12, 1, 4, 64, 21, 75, 128, 0},
+  };
+  for (const auto& c : cases) {
+    mlkv_map* mp = nullptr;
+    EXPECT(mlkv_map_create_uniform(c.l, c.h, c.m, c.g, &mp) == MLKV_OK);
+    mlkv_cache cache{addr(0x100000), addr(0x200000), c.m * c.g, c.B, c.S, c.D};
+    stub_prefills = 0;
+    EXPECT(mlkv_prefill_step(addr(0x300000), addr(0x300000), addr(0x300000), &cache, mp,
+                             lens(0x400000), c.T, addr(0x500000), MLKV_OUT_F32, nullptr) == MLKV_OK);
+    EXPECT(stub_prefills == 1 && stub_prefill_form == c.form);
+    stub_prefills = -1;
+    mlkv_map_destroy(mp);
+  }
+}
+
 extern long stub_steps;
 extern mlkv::StepParams stub_step;
 
@@ -220,6 +247,7 @@ int main() {
   maps();
   entry_points();
   prefill_grids();
+  prefill_forms();
   step_runs();
   model();
   std::printf("host driver: %d failure(s)\n", g_failures);

@@ -5,12 +5,13 @@
 // driver only exercises paths that stop before any launch, and an
 // unexpected MLKV_ERR_HIP would show that one was reached.  Prefill launches
 // succeed while stub_prefills counts them (not negative): the largest grid
-// of theirs, in threads along x as the device counts them, is kept.
-// Launches of decode steps succeed while stub_steps counts
+// of theirs, in threads along x as the device counts them, is kept, and the
+// last one's form.  Launches of decode steps succeed while stub_steps counts
 // them: the last one of a whole step is kept.
 #include "kernels.h"
 
 long stub_prefills = -1, stub_prefill_threads = 0;
+int stub_prefill_form = -1;
 long stub_steps = -1;
 mlkv::StepParams stub_step;
 
@@ -33,9 +34,10 @@ hipError_t launch_cache_rows(const CacheRowsParams&, int, hipStream_t) { return 
 hipError_t launch_append_rows(const AppendRowsParams&, int, int, hipStream_t) {
   return stub_prefills < 0 ? no_device() : hipSuccess;
 }
-hipError_t launch_prefill(const PrefillParams& p, int, hipStream_t, hipEvent_t, hipEvent_t) {
+hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t, hipEvent_t, hipEvent_t) {
   if (stub_prefills < 0) return no_device();
   ++stub_prefills;
+  stub_prefill_form = static_cast<int>(prefill_form(p, head_dim, compute_units()));
   const long threads = static_cast<long>(p.B) * p.n_groups * 256;
   stub_prefill_threads = threads > stub_prefill_threads ? threads : stub_prefill_threads;
   return hipSuccess;
