@@ -225,7 +225,9 @@ mlkv_status mlkv_decode_attention(int layer, const void* q, const mlkv_cache* ca
  *   ctx_lens: device int32 [batch], tokens cached before the step; the caller
  *             increments them after the step.
  *   out_all: device [l][batch][h][head_dim], fp32 or bf16.
- *   max_len_hint: bound of ctx_lens[b] + 1 (<= 0 means capacity).
+ *   max_len_hint: bound of ctx_lens[b] + 1 (<= 0 means capacity).  A bound
+ *             that is close to the lengths lets the step fit its workgroups
+ *             to them.
  * Every layer's queries are at hand, so where the map's layers fall into equal
  * groups of consecutive layers that read the same KV heads and whose first
  * layer appends them (every uniform map), all layers run in one launch and

@@ -340,7 +340,9 @@ Plan plan(const mlkv_map* map, int layer, int batch, int max_len, int head_dim) 
 // 16 a unit: 0.57 of the time at 250 tokens, 0.94 at 8000).  With one chunk
 // eight gain on grids of several rounds from about 1000 tokens (one block of
 // rows) or 2000 (two) on: up to 2 % on equal lengths, 1 to 10 % on ragged
-// ones, so they are taken where sequences of kLongTiles tiles are allowed.
+// ones, so they are taken where the caller's bound allows sequences of
+// kLongTiles tiles; without a bound the sequences may be short in a long cache,
+// where eight cost more (142 x 8 heads of 128 at 1 .. 8 tokens 14.5 / 21.9).
 struct StepPlan {
   int chunks, chunk_rows, runs, waves;
   long units;
@@ -350,7 +352,8 @@ constexpr int kLongTiles = 64;
 constexpr int kFullRun = 3 << 17;
 constexpr int kMaxStepChunksBySplit = 5;  // chunks a unit may be cut into to fill the device
 
-StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, size_t ws_bytes) {
+StepPlan step_plan(const mlkv_map* map, int batch, int max_len, bool bounded, int head_dim,
+                   size_t ws_bytes) {
   StepPlan pl{};
   const long cus = compute_units_or_fallback();
   const int rows = map->layers_per_group * map->group[0];
@@ -361,7 +364,7 @@ StepPlan step_plan(const mlkv_map* map, int batch, int max_len, int head_dim, si
   pl.chunk_rows = (rows + pl.chunks - 1) / pl.chunks;
   const long groups = pl.units * pl.chunks;  // workgroups without split runs
   const int max_tiles = tiles_of(max_len < 1 ? 1 : max_len);
-  const bool rounds = groups > 3 * cus && pl.chunks == 1 && max_tiles >= kLongTiles;
+  const bool rounds = bounded && groups > 3 * cus && pl.chunks == 1 && max_tiles >= kLongTiles;
   pl.waves = groups <= cus || rounds ? mlkv::wide_waves() : mlkv::default_waves();
   const long longest = max_tiles / kMinTiles;
   const long bound = mlkv::step_run_bound(max_tiles);
@@ -845,7 +848,7 @@ size_t mlkv_workspace_bytes(const mlkv_map* map, int batch, int capacity, int he
     best = need > best ? need : best;
   }
   if (best > 0 && map->layers_per_group > 0) {
-    const size_t need = step_plan(map, batch, capacity, head_dim, SIZE_MAX).need;
+    const size_t need = step_plan(map, batch, capacity, false, head_dim, SIZE_MAX).need;
     best = need > best ? need : best;
   }
   return best;
@@ -1067,7 +1070,8 @@ mlkv_status step_launch(const void* q_all, const uint16_t* k_new, const uint16_t
                         const double* inv_freq, int rope_half) {
   const int B = cache->batch, D = cache->head_dim;
   const int max_len = max_len_of(cache, max_len_hint);
-  const StepPlan pl = step_plan(map, B, max_len, D, workspace ? workspace_bytes : 0);
+  const StepPlan pl =
+      step_plan(map, B, max_len, max_len_hint > 0, D, workspace ? workspace_bytes : 0);
   char* base = static_cast<char*>(workspace);
   mlkv::StepParams p{};
   p.q = static_cast<const uint16_t*>(q_all);

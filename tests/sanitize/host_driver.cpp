@@ -228,6 +228,24 @@ static void step_runs() {
   }
 }
 
+// Several rounds of whole units: eight waves only where the caller's own bound
+// allows long sequences; a long cache may hold short ones.
+static void step_waves() {
+  mlkv_map* mp = nullptr;
+  EXPECT(mlkv_map_create_uniform(1, 32, 1, 8, &mp) == MLKV_OK);
+  mlkv_cache cache{addr(0x100000), addr(0x200000), 8, 142, 4096, 128};
+  for (const auto& c : {std::pair<int, int>{0, 4}, std::pair<int, int>{40, 4},
+                        std::pair<int, int>{4096, 8}}) {
+    stub_steps = 0;
+    EXPECT(mlkv_decode_step(addr(0x300000), addr(0x300000), addr(0x300000), &cache, mp,
+                            lens(0x400000), addr(0x500000), MLKV_OUT_F32, c.first, addr(0x600000),
+                            mlkv_workspace_bytes(mp, 142, 4096, 128), nullptr) == MLKV_OK);
+    EXPECT(stub_steps == 1 && stub_step.waves == c.second);
+    stub_steps = -1;
+  }
+  mlkv_map_destroy(mp);
+}
+
 static void model() {
   mlkv_map* mp = nullptr;
   EXPECT(mlkv_map_create_uniform(2, 4, 1, 1, &mp) == MLKV_OK);
@@ -249,6 +267,7 @@ int main() {
   prefill_grids();
   prefill_forms();
   step_runs();
+  step_waves();
   model();
   std::printf("host driver: %d failure(s)\n", g_failures);
   return g_failures == 0 ? 0 : 1;

@@ -32,10 +32,11 @@ def _lengths(B, top):
 
 
 def _step(dw, out_dtype=torch.float32, ws=None, rd=0):
-    w = dw.w
+    w = dw.w  # dw.hint: the caller's bound of the lengths, if any
     out = torch.full((w.l, w.B, w.h, w.D), float("nan"), dtype=out_dtype, device="cuda")
     mlkv.decode_step(dw.q, dw.k_new, dw.v_new, dw.cache, dw.map, dw.ctx, out,
-                     ws=dw.ws if ws is None else ws, rotary_dims=rd)
+                     max_len_hint=getattr(dw, "hint", 0), ws=dw.ws if ws is None else ws,
+                     rotary_dims=rd)
     torch.cuda.synchronize()
     return out.float().cpu().numpy()
 
@@ -258,7 +259,7 @@ def test_rows_without_a_score_are_nan_and_empty_rows_zero(l, h, m, g, D, B, top)
     (4, 32, 1, 4, 128, 193),
 ])
 def test_eight_waves_on_whole_units(l, h, m, g, D, B):
-    """Several rounds of workgroups over sequences allowed 64 tiles: eight
+    """Several rounds of workgroups over sequences bounded by 64 tiles: eight
     waves a unit, here with lengths from none to a few tiles and three long."""
     tag = f"eight waves l{l} h{h} m{m} g{g} D{D}"
     say(tag)
@@ -276,4 +277,5 @@ def test_eight_waves_on_whole_units(l, h, m, g, D, B):
     dw.cache = mlkv.Cache.empty(m * g, B, 2048, D)
     dw.cache.load_rows(dw.host["k_cache"], dw.host["v_cache"])
     dw.ws = mlkv.workspace(dw.map, B, 2048, D)
+    dw.hint = 2048
     _check(dw, tag)
