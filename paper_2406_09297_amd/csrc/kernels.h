@@ -286,14 +286,18 @@ inline PrefillForm prefill_form(const PrefillParams& p, int head_dim, long cus) 
   //       two a unit       37 / 41 at 2000, 23 / 23 at 800, 16 / 12 at 200
   // Plain blocks of few rows, one or two a unit: 133 / 177 at 8000 (64, 1.1 a
   // unit), 28 / 27 at 1500; above two 209 / 192.  128: 249 / 215.
+  // A prompt alone: its last block is the plain form's time, so from 640 tokens
+  // on it counts as long (64, three a unit: 500 tokens 17.4 / 15.6, 600 17.7 /
+  // 16.9, 700 17.2 / 18.2, 1000 20.2 / 22.6; 128, two: 18.2 / 18.0 at 600).
+  const bool long_call = p.S >= 1024 || p.T >= 640;
   if (head_dim == 64) {
     if (split <= cus) return PrefillForm::kSplit;
     if (plain < cus && split <= 2 * cus && p.S >= 512) return PrefillForm::kSplit;
-    if (plain < cus && split <= 3 * cus && p.S >= 1024) return PrefillForm::kSplit;
+    if (plain < cus && split <= 3 * cus && long_call) return PrefillForm::kSplit;
     return 4 * split <= 7 * cus && p.S >= 2048 ? PrefillForm::kSplit : PrefillForm::kPlain;
   }
   if (plain < cus && split <= cus && p.S >= 256) return PrefillForm::kSplit;
-  if (plain <= cus && (plain < cus || split == 2 * plain) && split <= 2 * cus && p.S >= 1024)
+  if (plain <= cus && (plain < cus || split == 2 * plain) && split <= 2 * cus && long_call)
     return PrefillForm::kSplit;
   // Wide blocks read the rows a third or a quarter as often.  They pay from two
   // a unit on for long contexts (93 / 101, 2 x 2048 tokens of 32 heads) and for

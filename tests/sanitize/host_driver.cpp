@@ -166,6 +166,8 @@ static void prefill_forms() {
       {1, 32, 1, 32, 128, 101, 1, 64, 0},  {1, 12, 1, 12, 128, 80, 1, 64, 0},
       {12, 12, 12, 12, 128, 126, 2, 64, 0}, {1, 32, 1, 32, 128, 41, 26, 64, 0},
       {1, 32, 1, 8, 64, 5, 129, 256, 0},   {1, 12, 1, 4, 64, 21, 75, 128, 0},
+      {1, 12, 1, 1, 64, 2, 822, 832, 1},   {1, 12, 1, 1, 64, 4, 500, 512, 0},
+      {1, 12, 1, 1, 128, 1, 800, 832, 1},
   };
   for (const auto& c : cases) {
     mlkv_map* mp = nullptr;
