@@ -816,9 +816,9 @@ def measure_decode(args, w, dev, headline: bool):
     torch.cuda.synchronize()
     ms_warm = e0.elapsed_time(e1) / args.steps
 
-    # (3) Per launch, cold: a flush before every layer's attention
-    # (mlkv_decode_attention; the pair brackets the merge kernel too when
-    # one follows).  This is the roofline's figure.
+    # (3) Per launch, cold: a flush before every layer's attention as its own
+    # call (mlkv_decode_attention; the pair brackets the merge kernel too when
+    # one follows): the roofline's figure of the one-layer kernel.
     log("[bench] cold attention launches")
     lens_attn = (ctx + 1).to(torch.int32)
     out_l = torch.empty((w.B, w.h, w.D), dtype=torch.float32, device=dev)
@@ -832,6 +832,15 @@ def measure_decode(args, w, dev, headline: bool):
     torch.cuda.synchronize()
     c_n, _, c_min, c_max = mlkv.profile_read()
     c_dur = mlkv.profile_durations(c_n)
+    mlkv.profile_disable()
+    # ... and before every step: its own launches, one where all layers share it.
+    s_reps = min(args.steps, 30)
+    mlkv.profile_enable(s_reps * w.l)
+    for _ in range(s_reps):
+        flush_caches(flush, sink)
+        one_step()
+    torch.cuda.synchronize()
+    s_n, s_tot, s_min, s_max = mlkv.profile_read()
     mlkv.profile_disable()
     del flush
     torch.cuda.empty_cache()
@@ -858,6 +867,8 @@ def measure_decode(args, w, dev, headline: bool):
     # A step in one launch reads each cached byte once for all its layers.
     once = kv_bytes_once(w, inp["ctx"]) + sum(x["q"] + x["out"] for x in per_layer)
     w_bytes = once if n_launch == args.steps else attn_bytes
+    s_bytes = once if s_n == s_reps else attn_bytes
+    s_avg = s_tot * 1e-3 / s_n
 
     workgroups, max_parts = mp.plan(0, w.B, S, w.D, max_len)
     floor = launch_floor(workgroups)
@@ -877,6 +888,16 @@ def measure_decode(args, w, dev, headline: bool):
         "p10_p50_p90_launch_us": [round(p10 * 1e3, 3), round(p50 * 1e3, 3), round(p90 * 1e3, 3)],
         "launches": c_n, "bytes_per_launch": int(attn_bytes),
         "cache_state": "Infinity Cache flushed (1 GiB read) before each launch: K/V from HBM",
+        "step_launch": {"kernel": "step_kernel" if s_n == s_reps else kernel,
+                        "avg_launch_us": round(s_avg * 1e6, 3),
+                        "min_launch_us": round(s_min * 1e3, 3),
+                        "max_launch_us": round(s_max * 1e3, 3),
+                        "achieved": round(s_bytes / s_avg / 1e9, 1),
+                        "frac": round(s_bytes / s_avg / 1e9 / HBM_PEAK_GBS, 4),
+                        "launches": s_n, "bytes_per_launch": int(s_bytes),
+                        "cache_state": "what the timed step launches, Infinity Cache flushed "
+                                       "before each step; the figures above are of one layer's "
+                                       "attention as a call of its own"},
         "warm": {"avg_launch_us": round(w_avg * 1e6, 3),
                  "achieved": round(w_bytes / w_avg / 1e9, 1),
                  "frac": round(w_bytes / w_avg / 1e9 / HBM_PEAK_GBS, 4),

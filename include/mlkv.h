@@ -232,8 +232,9 @@ mlkv_status mlkv_decode_attention(int layer, const void* q, const mlkv_cache* ca
  * groups of consecutive layers that read the same KV heads and whose first
  * layer appends them (every uniform map), all layers run in one launch and
  * each cached row is read once for all layers sharing it.  Other maps, steps
- * under one of the plan overrides below, and steps of more than about four
- * million (sequence, KV head) units run layer by layer.  A workspace smaller
+ * under one of the plan overrides below, steps of more than about four million
+ * (sequence, KV head) units and steps of a one-layer map over up to three very
+ * long units run layer by layer.  A workspace smaller
  * than mlkv_workspace_bytes that holds the layer-by-layer step's needs is
  * accepted; the one-launch step then cuts sequences into fewer runs.
  */
@@ -252,9 +253,9 @@ mlkv_status mlkv_decode_step(const void* q_all, const void* k_new_all, const voi
  * object when the library is loaded on a device, held until the process
  * ends); this call allocates nothing.  The first call on a device looks up
  * the scratch's address and zero-fills it on `stream`.
- * A step whose workspace need (that of mlkv_decode_step for these arguments;
- * at most mlkv_workspace_bytes) exceeds 16 MiB is rejected with
- * MLKV_ERR_WORKSPACE before anything is launched.  Every call on a device
+ * A step whose layer-by-layer workspace need for these arguments (at most
+ * mlkv_workspace_bytes) exceeds 16 MiB is rejected with MLKV_ERR_WORKSPACE
+ * before anything is launched, also where it would run in one launch.  Every call on a device
  * shares that device's scratch: calls that overlap on one device (on
  * different streams, or from different threads without ordering) race and
  * give wrong results; order them on one stream.
@@ -268,19 +269,20 @@ mlkv_status mlkv_decode_step_noalloc(const void* q_all, const void* k_new_all,
 /*
  * mlkv_decode_step with the rotary position embedding of the GPT-NeoX
  * architecture that the paper's Pythia models use (Section 4.2) applied to
- * the newest token inside the step: each attention launch rotates the
- * queries it loads and each owning layer rotates the new keys before storing
- * them, so the cache holds rotated keys.  q_all and k_new_all are read only
+ * the newest token inside the step: its attention launches (one, where all
+ * layers run in one) rotate the queries they load, and the new keys are
+ * rotated before they are stored, so the cache holds rotated keys.  q_all and k_new_all are read only
  * (never written): repeating a call on the same buffers, or replaying it
  * from a captured graph, gives the same outputs and cache.
  * Rotation: channel pairs (j, j + rotary_dims/2), j < rotary_dims/2, of each
  * head vector turn by ctx_lens[b] * rotary_base^(-2j/rotary_dims) radians;
- * the cosine and sine are tabulated once per step in double (in the first
- * mlkv_workspace_bytes_rope - mlkv_workspace_bytes bytes of the workspace),
- * each rotated value is computed in double (products and sum each rounded)
- * and rounded once to bf16, nearest even; channels at or past rotary_dims
- * and the values are not rotated.  Pythia-160M: rotary_dims 16, rotary_base
- * 10000.
+ * the cosine and sine are taken in double, by the workgroups of a step in one
+ * launch, or where those are many rounds, or layers run by themselves, once
+ * per step (tabulated in the first mlkv_workspace_bytes_rope -
+ * mlkv_workspace_bytes bytes of the workspace); each rotated value is
+ * computed in double (products and sum each rounded) and rounded once to
+ * bf16, nearest even; channels at or past rotary_dims and the values are not
+ * rotated.  Pythia-160M: rotary_dims 16, rotary_base 10000.
  *   rotary_dims: a multiple of 16 in [0, head_dim] (else
  *                MLKV_ERR_UNSUPPORTED); 0 is mlkv_decode_step.
  *   rotary_base: positive and finite (else MLKV_ERR_INVALID_ARG).

@@ -10,7 +10,7 @@ namespace mlkv {
 // Rotary position embedding of the newest token (GPT-NeoX: rotate-half pairs
 // (j, j + half) of the first 2*half channels of every head vector).  Once per
 // step the cosine and sine of each pair's angle at the token's position are
-// tabulated in double, cs[(b*half + j)*2 + {0, 1}]; the attention launches
+// tabulated in double, cs[(b*half + j)*2 + {0, 1}]; attention launches
 // rotate their queries and the owners' appends their keys from that table.
 // (A step of one launch and few workgroups takes them itself: StepParams.)
 // inv_freq[j] = base^(-2j/(2*half)): radians pair j turns by per position.

@@ -2,11 +2,12 @@
 //
 //   append_rows_kernel  the owners' new rows of a prompt -> cache slots
 //                       ctx_b .. ctx_b + T - 1 (bit copy)
-//   prefill_kernel      causal attention of one layer over the cache: token
-//                       t of sequence b attends positions 0 .. ctx_b + t
+//   prefill_kernel      causal attention of one layer, or of all layers of a
+//                       call, over the cache: token t of sequence b attends
+//                       positions 0 .. ctx_b + t
 //
-// The query rows of a KV head (T tokens x G heads of its group) are the MFMA
-// columns, 16 per wave; the tile arithmetic is the decode path's (tile.h).
+// The query rows of a KV head (T tokens x the heads of the layers that read
+// it) are the MFMA columns, 16 per block; the tile arithmetic is the decode path's (tile.h).
 // A separate translation unit, so that the decode kernels are compiled
 // exactly as on their own.
 #include <hip/hip_ext.h>
@@ -200,10 +201,10 @@ struct TileRing {
   }
 };
 
-// What bounds it: vector issue, 70 % of the cycles (the exponentials alone take
-// a third of it), beside matrix cores at 44 %.  696 us for the 12-layer MLKV-4
-// prompt of 8 x 2000 tokens in one launch, 849 TFLOP/s over the step; a launch
-// and an append per layer took 776 us, and 2560 against 351 us for 257 new
+// What bounds it: vector issue, 77 % of the busy cycles (the exponentials alone
+// take 29 % of it), beside matrix cores at 50 %.  704 us for the 12-layer MLKV-4
+// prompt of 8 x 2000 tokens in one launch, 838 TFLOP/s over the step; a launch
+// and an append per layer took 780 us, and 2723 against 382 us for 257 new
 // tokens on two prompts of about 14000, whose row blocks leave most of the
 // device idle layer by layer.
 template <int D, int NB>

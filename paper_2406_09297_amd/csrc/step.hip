@@ -14,11 +14,12 @@
 // from the sequence's own length; a workgroup is one run of one chunk.  The
 // last run of a unit to finish merges its runs.
 //
-// What bounds it: HBM for large steps (a 7B-like step of 17.2 GB in 2.90 ms,
-// 5.93 TB/s, where a plain streaming read reaches 6.0; one launch per layer
+// What bounds it: HBM for large steps (a 7B-like step of 17.2 GB in 2.92 ms,
+// 5.9 TB/s, where a plain streaming read reaches 6.0; one launch per layer
 // took 11.6 ms), the first and last round trips for small ones (one sequence
-// of 128 tokens 8.9 us against 46.8 us).  128 ragged sequences of 12-layer
-// MLKV-4: 42.4 us against 145 us; eight of 32768 tokens: 54 against 211 us.
+// of 128 tokens 8.9 us against 46.8 us, 5.9 of them on the device).  128 ragged
+// sequences of 12-layer MLKV-4: 43.5 us against 145 us; eight of 32768 tokens:
+// 55 against 211 us.
 // A third tile in flight per wave spills (184 us) and is no faster where it
 // fits; eight waves on a unit shorten the stream of a lone workgroup but hold
 // fewer workgroups per compute unit, so the host gives eight waves to grids of
