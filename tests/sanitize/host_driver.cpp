@@ -230,6 +230,52 @@ static void step_runs() {
   }
 }
 
+// Every map of four layers of two heads on up to three KV heads: a step takes
+// all layers in one launch exactly where the launch's arithmetic (KV head from
+// layer group and place in it, the group's first layer appending) is the map's.
+static void one_launch_maps() {
+  long one = 0, by_layer = 0;
+  for (int n_kv = 1; n_kv <= 3; ++n_kv) {
+    std::vector<std::pair<int, int>> reads;  // (first KV head, count) of a layer
+    for (int c = 1; c <= 2; ++c)
+      for (int lo = 0; lo + c <= n_kv; ++lo) reads.push_back({lo, c});
+    const int nr = static_cast<int>(reads.size()), tables = nr * nr * nr * nr;
+    for (int t = 0; t < tables; ++t)
+      for (int o = 0; o < 1 << (2 * n_kv); ++o) {
+        int32_t kv_of[8], owner_of[3];
+        for (int n = 0, x = t; n < 4; ++n, x /= nr)
+          for (int i = 0; i < 2; ++i) kv_of[2 * n + i] = reads[x % nr].first + i * (reads[x % nr].second - 1);
+        for (int kv = 0; kv < n_kv; ++kv) owner_of[kv] = o >> (2 * kv) & 3;
+        mlkv_map* mp = nullptr;
+        if (mlkv_map_create(4, 2, n_kv, kv_of, owner_of, &mp) != MLKV_OK) continue;
+        mlkv_cache cache{addr(0x100000), addr(0x200000), n_kv, 1, 32, 64};
+        stub_steps = 0;
+        EXPECT(mlkv_decode_step(addr(0x300000), addr(0x300000), addr(0x300000), &cache, mp,
+                                lens(0x400000), addr(0x500000), MLKV_OUT_F32, 0, addr(0x600000),
+                                1 << 20, nullptr) == MLKV_OK);
+        bool grouped = false;  // some group size for which the arithmetic is the map's
+        for (int per = 1; per <= 4; per *= 2) {
+          const int g = n_kv * per / 4;  // KV heads of a layer
+          if (g * 4 != n_kv * per || g < 1 || g > 2) continue;
+          bool same = true;
+          for (int n = 0; n < 4; ++n)
+            for (int i = 0; i < 2; ++i)
+              same = same && kv_of[2 * n + i] == n / per * g + i / (2 / g);
+          for (int kv = 0; kv < n_kv; ++kv) same = same && owner_of[kv] == kv / g * per;
+          grouped = grouped || same;
+          if (same && stub_steps == 1)
+            EXPECT(stub_step.layers == per && stub_step.kv_per_layer == g &&
+                   stub_step.G == 2 / g && stub_step.n_kv == n_kv);
+        }
+        EXPECT(stub_steps == (grouped ? 1 : 0));
+        (stub_steps == 1 ? one : by_layer) += 1;
+        stub_steps = -1;
+        mlkv_map_destroy(mp);
+      }
+  }
+  EXPECT(one >= 3 && by_layer > 100);
+}
+
 // Several rounds of whole units: eight waves only where the caller's own bound
 // allows long sequences; a long cache may hold short ones.
 static void step_waves() {
@@ -270,6 +316,7 @@ int main() {
   prefill_forms();
   step_runs();
   step_waves();
+  one_launch_maps();
   model();
   std::printf("host driver: %d failure(s)\n", g_failures);
   return g_failures == 0 ? 0 : 1;

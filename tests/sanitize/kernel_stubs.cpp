@@ -28,7 +28,9 @@ hipError_t launch_norm2(const NormParams&, hipStream_t) { return no_device(); }
 hipError_t launch_qkv_epilogue(const QkvEpilogueParams&, hipStream_t) { return no_device(); }
 hipError_t launch_gelu(const GeluParams&, hipStream_t) { return no_device(); }
 hipError_t launch_residual(const ResidualParams&, hipStream_t) { return no_device(); }
-hipError_t launch_append(const AppendParams&, int, int, hipStream_t) { return no_device(); }
+hipError_t launch_append(const AppendParams&, int, int, hipStream_t) {
+  return stub_steps < 0 ? no_device() : hipSuccess;
+}
 hipError_t launch_rope_table(const RopeTableParams&, hipStream_t) { return no_device(); }
 hipError_t launch_cache_rows(const CacheRowsParams&, int, hipStream_t) { return no_device(); }
 hipError_t launch_append_rows(const AppendRowsParams&, int, int, hipStream_t) {
