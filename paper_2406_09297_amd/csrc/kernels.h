@@ -279,13 +279,13 @@ inline PrefillForm prefill_form(const PrefillParams& p, int head_dim, long cus) 
   // Split over the tokens where the plain form leaves compute units idle: it
   // shortens their streams, but every 32 rows read the context again and its
   // waves are merged, so the more blocks, the longer the contexts it needs.
-  //   64: one block a unit 53 / 131 at 6000 positions, 12 / 12 at none
-  //       two a unit       24 / 37 at 2000, 14 / 16 at 400
-  //       three a unit     26 / 31 at 1600, 26 / 26 at 1000, 15 / 12 at none
-  //   128: one a unit      48 / 100 at 6000, 12 / 11 at none
-  //       two a unit       37 / 41 at 2000, 23 / 23 at 800, 16 / 12 at 200
-  // Plain blocks of few rows, one or two a unit: 133 / 177 at 8000 (64, 1.1 a
-  // unit), 28 / 27 at 1500; above two 209 / 192.  128: 249 / 215.
+  //   64: one block a compute unit 71 / 131 at 6000 positions, 12 / 12 at none
+  //       two 23 / 38 at 2000, 14 / 16 at 400
+  //       2.25 27 / 31 at 1600, 25 / 26 at 1200, 15 / 12 at none
+  //   128: 0.9 46 / 100 at 6000, 12 / 11 at none
+  //       two 36 / 41 at 2000, 23 / 23 at 800, 1.4 16 / 12 at 200
+  // Plain blocks of few rows, more than one: 64, 1.1 128 / 169 at 8000, 27 / 27
+  // at 1500; above two 211 / 192 at 8000; 128, 1.03 249 / 215 at 8000.
   // A prompt alone: its last block is the plain form's time, so from 640 tokens
   // on it counts as long (64, three a unit: 500 tokens 17.4 / 15.6, 600 17.7 /
   // 16.9, 700 17.2 / 18.2, 1000 20.2 / 22.6; 128, two: 18.2 / 18.0 at 600).
@@ -301,10 +301,10 @@ inline PrefillForm prefill_form(const PrefillParams& p, int head_dim, long cus) 
     return PrefillForm::kSplit;
   // Wide blocks read the rows a third or a quarter as often.  They pay from two
   // a unit on for long contexts (93 / 101, 2 x 2048 tokens of 32 heads) and for
-  // more rows than the caches near the units hold (233 / 295, 157 MiB on 400
+  // more rows than the caches near the units hold (233 / 295, 150 MiB on 400
   // positions); of several rounds for a quarter of it (259 / 328, 69 MiB), and
   // of units not a multiple of eight, whose blocks go to other XCDs, for less
-  // (144 / 188, 43 MiB).  Short ones keep the plain form (44 / 34, 128 units of
+  // (120 / 188, 43 MiB).  Short ones keep the plain form (44 / 34, 128 units of
   // 1200 rows on none), and mostly empty blocks (37 / 16, units of one row).
   // Half as often pays on several rounds (182 / 285, 768 units of 100 rows).
   const long wide = blocks(kPrefillWideRows), mib = units * p.S * 512 >> 20;
